@@ -145,7 +145,7 @@ typedef struct {
     int32_t autotune;           /* 1: if this handle has not been tuned, time
                                    the sweep's launch shapes (waves per block
                                    that divide N(N+2)/8, FP32 fixup sweeps also
-                                   with per-XCD ticket queues, the column-relay
+                                   with per-XCD ticket queues, the tile
                                    shapes; full, 3/4 and 1/2 resident grid) at the
                                    first iteration of this call and keep the
                                    fastest for the handle's later calls; results
@@ -215,8 +215,9 @@ typedef struct {
     int32_t sweep_xcd_queues;      /* > 0: the sweep takes tickets from that many
                                       per-XCD queues (faces stay in each XCD's
                                       L2); 0: one global queue                   */
-    int32_t sweep_relay;           /* > 0: column-relay sweep (see
-                                      dsn_set_sweep_shape) with this many roles  */
+    int32_t sweep_relay;           /* > 0: tile sweep of the shape
+                                      (sweep_waves_per_block, sweep_relay), see
+                                      dsn_set_sweep_shape                        */
 } dsn_solve_info;
 
 /* Validates the description, derives the quadrature and the moment tables on
@@ -339,14 +340,17 @@ dsn_status dsn_dose(dsn_problem *p, const double *phi, int32_t n, const double *
  *     global ticket queue, else the device's XCD count (dsn_xcd_queues) for
  *     the per-XCD queues, which are built for FP32 with the fixup and up to 4
  *     waves per block.
- *   relay = R > 0: column-relay items (a whole row of pencils along y,
- *     waves_per_block directions, R waves per direction taking the pencils in
- *     turn and handing their y faces to each other in LDS, so y faces never
- *     reach memory); built for (waves_per_block, R) = (1, 2), (1, 4), (2, 2),
- *     (2, 4) in FP32 and (1, 2), (1, 4) in FP64, with xcd_queues 0; needs LDS
- *     for one pencil's y faces per wave (nx x 32 bytes in FP32), so large
- *     x extents may not fit.  The adjoint's sweeps of such a handle use
- *     pencil items of waves_per_block directions.
+ *   relay = R > 0: tile items (the pencils of a rectangle of 8 x 8 columns,
+ *     one direction, a wave per pencil; the waves hand their y and z faces to
+ *     each other in LDS, so only the faces on the tile's rim reach memory);
+ *     (waves_per_block, R) picks the block: in FP32 (1, 2) one team of 4
+ *     waves, (2, 2) two of 4, (1, 4) one of 16, (2, 4) two of 8; in FP64
+ *     (1, 2) one of 4, (1, 4) one of 8; waves_per_block must divide the
+ *     directions of an octant, xcd_queues be 0, and waves_per_block x R
+ *     pencils of the x extent fit a compute unit's LDS (nx up to 970 for
+ *     (1, 4) in FP32, 357 in FP64).  The tile's rectangle follows from the
+ *     mesh.  The default shape of an untuned handle is one of these where
+ *     the pencils' dependency chain bounds the sweep.
  * blocks per launch: 1..2^20 (the sweep's persistent blocks take work from a
  * ticket queue, so any count is correct and about the resident count is
  * fastest).  Every shape gives the same results bit for bit.  The handle
@@ -354,14 +358,14 @@ dsn_status dsn_dose(dsn_problem *p, const double *phi, int32_t n, const double *
  * while a solve on the handle runs.  DSN_ERR_INVALID_ARG (checked before any
  * device call) for a NULL handle, a shape that is not built, blocks out of
  * range or negative counts; DSN_ERR_UNSUPPORTED for per-XCD queues this
- * handle or device cannot use or a column-relay shape whose LDS does not
- * fit; DSN_ERR_DEVICE without a device. */
+ * handle or device cannot use or a tile shape beyond its x extents;
+ * DSN_ERR_DEVICE without a device. */
 dsn_status dsn_set_sweep_shape(dsn_problem *p, int32_t waves_per_block, int32_t blocks, int32_t xcd_queues,
                                int32_t relay);
 
 /* Host-only query: the sweep launch shapes the handle's autotune timed, in
  * the order timed.  Writes up to cap entries of waves per block, blocks per
- * launch, per-XCD queues (0: one global queue), column-relay roles (0:
+ * launch, per-XCD queues (0: one global queue), the tile shape's R (0:
  * pencil items) and milliseconds per sweep (negative: the shape's angular
  * fluence differed from the default shape's and it was not used); each
  * pointer may be NULL.  Returns the number timed (0 before any autotune;

@@ -97,7 +97,8 @@ struct SolveArgs {
     int sweep_grid;           // blocks launched
     int sweep_wpb;            // waves per block: directions of an octant sharing a pencil item
     int sweep_xcd;            // > 0: per-XCD ticket queues (octant o on XCD o mod sweep_xcd), faces in L2
-    int sweep_relay;          // > 0: column-relay sweep with this many roles (pencils handed over in LDS)
+    int sweep_relay;          // > 0: tile sweep (k_sweep_tile) of the shape (sweep_wpb, sweep_relay)
+    int tile_y, tile_z;       // its tile, in pencils (set at the launch)
     int sweep_mode;           // cell mode: 0 DD, 1 fixup, 2 fixup recording the fixed axes into mask,
                               // 3 transposed fixup cell with the fixed axes read from mask (adjoint)
     uint8_t *mask;            // [Nd][Vp] fixed-axis sets (modes 2 and 3), else null
@@ -126,16 +127,6 @@ struct SolveArgs {
     const int *seg;
     int nseg;
 };
-
-// The sweep runs as column-relay items: relay roles set, a forward cell mode
-// (pure DD or the fixup) and directions along +Omega.  Other sweeps of a
-// handle with such a shape (the adjoint's) use pencil items of the same
-// directions per block.
-template <typename T>
-__host__ __device__ inline bool sweep_uses_col(const SolveArgs<T> &a)
-{
-    return a.sweep_relay > 0 && (a.sweep_mode == 0 || a.sweep_mode == 1) && !a.rev;
-}
 
 // The per-source view of a batched argument block.
 template <typename T>
@@ -179,9 +170,10 @@ int sweep_wpb(int D, bool fp64);
 int sweep_wpb_choices(bool fp64, int *out);  // waves-per-block values built; returns the count (<= 16)
 template <typename T>
 int sweep_grid(int wpb, int mode, int n_cu);
-int sweep_col_choices(bool fp64, int *w_out, int *r_out);  // (directions, roles) of the built column-relay sweeps
+int sweep_tile_choices(bool fp64, int *w_out, int *r_out);  // (teams, r) of the built tile sweeps
+void sweep_tile(bool fp64, int w, int r, int NJ, int NK, int *ty, int *tz);  // the tile of a team, in pencils
 template <typename T>
-int sweep_grid_col(int w, int r, int mode, int nx, int n_cu);
+int sweep_grid_tile(int w, int r, int mode, int nx, int n_cu);
 // ev_before / ev_after (may be null): recorded on s right around the sweep
 // kernel itself (after the ticket reset, before the parity flip)
 template <typename T>

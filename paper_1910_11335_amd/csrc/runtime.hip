@@ -165,11 +165,11 @@ struct StageTimer {
 struct SweepShape {
     int wpb = 0, blocks = 0, xcd = 0;  // xcd: per-XCD queues (0 = one global queue)
     float ms = 0.f;                    // < 0: its angular fluence differed from the default shape's (not used)
-    int relay = 0;                     // > 0: column-relay sweep with wpb directions and this many roles per block
+    int relay = 0;                     // > 0: tile sweep of the shape (wpb, relay)
 };
 constexpr int kMaxWpb = 16;     // waves per block: largest value built is below this
-constexpr int kMaxShapes = 64;  // (waves-per-block choices + per-XCD-queue + column-relay variants) x grid {1, 3/4, 1/2}
-constexpr int kMaxCol = 8;      // column-relay (directions, roles) choices
+constexpr int kMaxShapes = 64;  // (waves-per-block choices + per-XCD-queue + tile variants) x grid {1, 3/4, 1/2}
+constexpr int kMaxTile = 8;     // tile shapes (teams, r)
 constexpr int kCtrInts = 16;    // sweep counter block: ticket, abort flag, epoch, per-XCD tickets
 // Polls of an upstream face word before a sweep gives up (about 1-2 us each
 // under load, so several seconds): far above any wait of a sweep that
@@ -201,16 +201,18 @@ struct DeviceState {
     Ctl *h_ctl = nullptr;  // pinned host mirror
     int *sweep_ctr = nullptr, *sweep_dstart = nullptr;
     int sweep_nitems = 0, sweep_grid = 0;  // sweep_nitems: items of one source
+    int n_cu = 0;                          // compute units of the device
+    double rounds_beside = 0.0;            // sweep_rounds of the problems solved beside this one
     // sweep launch shape: waves per block and its resident grid per choice
     int wpb = 0;
     int xcd_nq = 0;   // XCDs, when workgroup i was seen to run on XCD i mod xcd_nq (else 0)
     int xcd_use = 0;  // per-XCD queues in use (0 or xcd_nq)
-    int relay = 0;    // column-relay roles in use (0: pencil items)
-    // column-relay shapes built: (directions, roles) and their resident grid (0: does not fit)
-    int col_w[kMaxCol] = {}, col_r[kMaxCol] = {}, col_grid[kMaxCol] = {};
-    int ncol = 0;
-    // kind of word the forward face buffers hold: -1 none (all invalid), 0
-    // sign-parity, 1 tagged
+    int relay = 0;    // > 0: tile items of the shape (wpb, relay) (0: pencil items)
+    // tile shapes built: (teams, r) and their resident grid (0: not for this x extent)
+    int tile_w[kMaxTile] = {}, tile_r[kMaxTile] = {}, tile_grid[kMaxTile] = {};
+    int ntile = 0;
+    // what the forward face buffers hold: -1 nothing (all invalid), else the
+    // codec and item geometry of the last sweep (sweep_forward_faces)
     int face_tagged = -1;
     int grid_of[kMaxWpb + 1] = {};
     unsigned long long *csum = nullptr;  // autotune checksums
@@ -218,7 +220,7 @@ struct DeviceState {
     SweepShape tune_log[kMaxShapes];
     int tune_n = 0;
     // per-source buffers are sized for S_cap sources of a batch
-    int S_cap = 0, dstart_S = 0, dstart_wpb = 0;
+    int S_cap = 0, dstart_S = 0, dstart_wpb = 0, dstart_relay = 0;
     double *src_par = nullptr;
     int *face_par = nullptr;
     int S_cap_alloc = 0;  // sources the per-source buffers were sized for
@@ -275,34 +277,97 @@ struct Sizes {
     }
 };
 
-// Persistent sweep queue: items = 8 octants x direction groups x pencils
-// (relay > 0: x rows of pencils, one item sweeping a whole row).
-int sweep_items(const dsn_problem *p, int wpb, int relay = 0)
+// The grid of sweep items of one direction group (pencils, or tiles of
+// pencils for a tile shape) and the direction groups of an octant.
+struct ItemGrid {
+    int nj, nk, ngrp;
+};
+ItemGrid item_grid(const dsn_problem *p, int wpb, int relay)
 {
-    return 8 * (p->D / wpb) * (relay > 0 ? 1 : p->geom.NJ) * p->geom.NK;
+    const int NJ = p->geom.NJ, NK = p->geom.NK;
+    if (relay == 0) return {NJ, NK, p->D / wpb};
+    int ty = 1, tz = 1;
+    sweep_tile(p->precision == DSN_FP64, wpb, relay, NJ, NK, &ty, &tz);
+    return {(NJ + ty - 1) / ty, (NK + tz - 1) / tz, p->D};
 }
 
-// Resident grid of a column-relay shape, 0 if it is not built or does not fit.
-int col_grid_of(const DeviceState &d, int w, int r)
+// Persistent sweep queue: items = 8 octants x direction groups x pencils
+// (tiles).
+int sweep_items(const dsn_problem *p, int wpb, int relay = 0)
 {
-    for (int i = 0; i < d.ncol; ++i)
-        if (d.col_w[i] == w && d.col_r[i] == r) return d.col_grid[i];
+    const ItemGrid q = item_grid(p, wpb, relay);
+    return 8 * q.ngrp * q.nj * q.nk;
+}
+
+// Resident grid of a tile shape, 0 if it is not built or not for this x extent.
+int tile_grid_of(const DeviceState &d, int w, int r)
+{
+    for (int i = 0; i < d.ntile; ++i)
+        if (d.tile_w[i] == w && d.tile_r[i] == r) return d.tile_grid[i];
     return 0;
 }
 
-// First ticket of every pencil diagonal (tickets go diagonal by diagonal, all
-// sources of the batch and all direction groups inside each diagonal), plus
-// the total.
-std::vector<int> diagonal_starts(const dsn_problem *p, int S, int wpb)
+// The launch shape of a handle that has not been tuned, for S sources at a
+// time.  Tiles win where the chain of pencils bounds the sweep, pencils where
+// the memory does; what tells them apart is the number of rounds in which the
+// resident waves (16 a CU in FP32, 8 in FP64) sweep the pencil-directions.
+// Measured per sweep, pencil default against tile (us): 1.2 rounds (64^3 S8
+// FP32) 167 / 114, 5 rounds (128^3 S8 FP32) 439 / 382, 5.6 rounds (8 sources,
+// 48^3 S8 FP32) 215 / 217, 9 rounds (64^3 S16 FP64) 370 / 383, 18 rounds
+// (128^3 S16 FP32) 1102 / 1151.  The large tile saves hops through memory but
+// puts a direction's waves on one CU: it wins while the machine is not full
+// (64^3 S8 114 / 118, 40^3 S8 65 / 76, 20x100x30 S8 87 / 105) unless the pencils
+// are long (100x20x30 S8 78 / 71) or leave much of it idle.
+// Problems of a batch that sweep beside this one (on other streams) fill the
+// machine too: rounds_beside counts theirs.
+double sweep_rounds(const dsn_problem *p, int S, int n_cu)
 {
-    const int NJ = p->geom.NJ, NK = p->geom.NK;
-    const int ngrp = p->D / wpb;
-    std::vector<int> ds(NJ + NK + 1, 0);
+    return (double)S * p->Nd * p->geom.NJ * p->geom.NK / ((double)n_cu * (p->precision == DSN_FP64 ? 8 : 16));
+}
+SweepShape default_shape(const dsn_problem *p, int S, int n_cu, double rounds_beside)
+{
+    const bool fp64 = p->precision == DSN_FP64;
+    const int NJ = p->geom.NJ, NK = p->geom.NK, pens = NJ * NK;
+    auto tile_blocks = [&](int w, int r) {
+        return fp64 ? sweep_grid_tile<double>(w, r, p->fixup, p->geom.nx, n_cu)
+                    : sweep_grid_tile<float>(w, r, p->fixup, p->geom.nx, n_cu);
+    };
+    SweepShape x;
+    const double rounds = sweep_rounds(p, S, n_cu) + rounds_beside;
+    if (pens > 1 && rounds < 8.0) {
+        int ty = 1, tz = 1;
+        sweep_tile(fp64, 1, 4, NJ, NK, &ty, &tz);
+        const int slots = (NJ + ty - 1) / ty * ty * ((NK + tz - 1) / tz) * tz;
+        x.wpb = 1;
+        x.relay = rounds <= 1.5 && p->geom.nx <= 64 && 4 * pens >= 3 * slots ? 4 : 2;
+        x.blocks = tile_blocks(x.wpb, x.relay);
+        if (x.blocks > 0) return x;
+    }
+    x.relay = 0;
+    x.wpb = sweep_wpb(p->D, fp64);
+    x.blocks = fp64 ? sweep_grid<double>(x.wpb, p->fixup, n_cu) : sweep_grid<float>(x.wpb, p->fixup, n_cu);
+    return x;
+}
+
+// First ticket of every diagonal of items (tickets go diagonal by diagonal,
+// all sources of the batch and all direction groups inside each diagonal),
+// plus the total: nj + nk + 1 entries.
+void diagonal_starts(const ItemGrid &q, int S, int *ds)
+{
+    const int NJ = q.nj, NK = q.nk, ngrp = q.ngrp;
+    ds[0] = 0;
     for (int dd = 0; dd <= NJ + NK - 2; ++dd) {
         const int lo = std::max(0, dd - (NK - 1)), hi = std::min(dd, NJ - 1);
         ds[dd + 1] = ds[dd] + (hi - lo + 1) * 8 * ngrp * S;
     }
     ds[NJ + NK] = ds[NJ + NK - 1];
+}
+
+std::vector<int> diagonal_starts(const dsn_problem *p, int S, int wpb, int relay)
+{
+    const ItemGrid q = item_grid(p, wpb, relay);
+    std::vector<int> ds(q.nj + q.nk + 1);
+    diagonal_starts(q, S, ds.data());
     return ds;
 }
 
@@ -493,11 +558,19 @@ dsn_status ensure_batch(dsn_problem *p, int S)
             return fail(DSN_ERR_OUT_OF_MEMORY, "hipHostMalloc failed");
         d.S_cap = S;
     }
-    if (d.dstart_S != S || d.dstart_wpb != d.wpb) {
-        const std::vector<int> ds = diagonal_starts(p, S, d.wpb);
+    if (!d.tuned) {
+        const SweepShape x = default_shape(p, S, d.n_cu, d.rounds_beside);
+        d.wpb = x.wpb;
+        d.sweep_grid = x.blocks;
+        d.relay = x.relay;
+        d.sweep_nitems = sweep_items(p, d.wpb, d.relay);
+    }
+    if (d.dstart_S != S || d.dstart_wpb != d.wpb || d.dstart_relay != d.relay) {
+        const std::vector<int> ds = diagonal_starts(p, S, d.wpb, d.relay);
         DSN_HIP(hipMemcpy(d.sweep_dstart, ds.data(), ds.size() * sizeof(int), hipMemcpyHostToDevice));
         d.dstart_S = S;
         d.dstart_wpb = d.wpb;
+        d.dstart_relay = d.relay;
     }
     return DSN_OK;
 }
@@ -564,8 +637,7 @@ dsn_status ensure_device(dsn_problem *p)
     ALLOC(d.D0, s.D0);
     ALLOC(d.cdir, s.cdir);
     ALLOC(d.sig, s.sig);
-    d.wpb = sweep_wpb(p->D, p->precision == DSN_FP64);
-    d.sweep_nitems = sweep_items(p, d.wpb);
+    d.n_cu = prop.multiProcessorCount;
     ALLOC(d.sweep_ctr, kCtrInts * sizeof(int));
     ALLOC(d.csum, 2 * sizeof(unsigned long long));
     ALLOC(d.sweep_dstart, (size_t)std::max(p->geom.NJ + p->geom.NK + 1, 64) * sizeof(int));
@@ -610,17 +682,16 @@ dsn_status ensure_device(dsn_problem *p)
             if (p->D % wl[i] == 0 && wl[i] <= kMaxWpb)
                 d.grid_of[wl[i]] = f32 ? sweep_grid<float>(wl[i], p->fixup, prop.multiProcessorCount)
                                        : sweep_grid<double>(wl[i], p->fixup, prop.multiProcessorCount);  // mode = fixup
-        d.sweep_grid = d.grid_of[d.wpb];
-        int cw[kMaxCol], cr[kMaxCol];
-        const int nc = sweep_col_choices(!f32, cw, cr);
-        d.ncol = 0;
-        for (int i = 0; i < nc && d.ncol < kMaxCol; ++i) {
-            if (p->D % cw[i]) continue;
-            const int gr = f32 ? sweep_grid_col<float>(cw[i], cr[i], p->fixup, p->geom.nx, prop.multiProcessorCount)
-                               : sweep_grid_col<double>(cw[i], cr[i], p->fixup, p->geom.nx, prop.multiProcessorCount);
-            d.col_w[d.ncol] = cw[i];
-            d.col_r[d.ncol] = cr[i];
-            d.col_grid[d.ncol++] = gr;
+        int tw[kMaxTile], tr[kMaxTile];
+        const int nc = sweep_tile_choices(!f32, tw, tr);
+        d.ntile = 0;
+        for (int i = 0; i < nc && d.ntile < kMaxTile; ++i) {
+            if (p->D % tw[i]) continue;
+            d.tile_w[d.ntile] = tw[i];
+            d.tile_r[d.ntile] = tr[i];
+            d.tile_grid[d.ntile++] =
+                f32 ? sweep_grid_tile<float>(tw[i], tr[i], p->fixup, p->geom.nx, prop.multiProcessorCount)
+                    : sweep_grid_tile<double>(tw[i], tr[i], p->fixup, p->geom.nx, prop.multiProcessorCount);
         }
     }
     if (e != hipSuccess) {
@@ -780,6 +851,11 @@ dsn_status status_of(const Ctl *c, int G)
     return st;
 }
 
+// What the forward face buffers hold, besides the codec of single pencil
+// sweeps (0, 1): words of a fused batch, and from kFacesTile on words of a tile
+// sweep by tile and codec.
+constexpr int kFacesFused = 9, kFacesTile = 16;
+
 // A sweep on the forward face buffers.  Those hold the words of one codec at
 // a time: before a sweep that reads the other kind (a launch shape with
 // per-XCD queues after one without, a fixed-axis recording sweep after a
@@ -793,11 +869,15 @@ int sweep_forward_faces(dsn_problem *p, const SolveArgs<T> &a, int g, hipStream_
 {
     DeviceState &d = p->dev;
     if ((void *)a.faceY == d.faceY) {
-        // codec of the words; column-relay sweeps (+2) leave the y words
-        // alone, so those go stale
-        const bool col = sweep_uses_col(a);
-        const int tagged = col ? (a.sweep_mode == 0 ? 1 : 0) + 2
-                               : sweep_tagged_faces(sizeof(T) == 8, a.sweep_mode, a.sweep_wpb, a.sweep_xcd) ? 1 : 0;
+        // codec of the words; tile sweeps write the words of their tiles'
+        // rims only, in another order, so every tile geometry counts as a
+        // codec of its own
+        int tagged = sweep_tagged_faces(sizeof(T) == 8, a.sweep_mode, a.sweep_wpb, a.sweep_relay ? 0 : a.sweep_xcd) ? 1 : 0;
+        if (a.sweep_relay > 0) {
+            int ty = 0, tz = 0;
+            sweep_tile(sizeof(T) == 8, a.sweep_wpb, a.sweep_relay, a.g.NJ, a.g.NK, &ty, &tz);
+            tagged += kFacesTile + 2 * (ty + 32 * tz);
+        }
         if (d.face_tagged >= 0 && tagged != d.face_tagged) {
             hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
             if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return -1;
@@ -888,8 +968,8 @@ void tune_sweep(dsn_problem *p, SolveArgs<T> &a, int g, hipStream_t s)
     const int S = a.S;
     const long words = (long)S * p->Nd * p->geom.Vp * (long)(sizeof(T) / 4);
     std::vector<int> ds;
-    auto use_table = [&](int w) {  // diagonal starts for w waves per block (host copy kept until synced)
-        ds = diagonal_starts(p, S, w);
+    auto use_table = [&](int w, int relay) {  // the shape's diagonal starts (host copy kept until synced)
+        ds = diagonal_starts(p, S, w, relay);
         return hipMemcpyAsync(d.sweep_dstart, ds.data(), ds.size() * sizeof(int), hipMemcpyHostToDevice, s) ==
                hipSuccess;
     };
@@ -910,10 +990,10 @@ void tune_sweep(dsn_problem *p, SolveArgs<T> &a, int g, hipStream_t s)
     };
     // reference: the default shape
     unsigned long long ref = 0;
-    ok = ok && use_table(d.wpb);
+    ok = ok && use_table(d.wpb, d.relay);
     if (ok) {
         launch_m2d<T>(a, g, s);
-        sweep_forward_faces<T>(p, shape_args(d.wpb, d.sweep_grid, 0, 0), g, s);
+        sweep_forward_faces<T>(p, shape_args(d.wpb, d.sweep_grid, 0, d.relay), g, s);
         ok = checksum(0, ref);
     }
     struct Cand {
@@ -929,11 +1009,11 @@ void tune_sweep(dsn_problem *p, SolveArgs<T> &a, int g, hipStream_t s)
         if (d.xcd_nq > 0 && sweep_xcd_supported(sizeof(T) == 8, p->fixup, w))
             cands.push_back({w, d.xcd_nq, 0, d.grid_of[w]});
     }
-    for (int i = 0; i < d.ncol; ++i)
-        if (d.col_grid[i] > 0) cands.push_back({d.col_w[i], 0, d.col_r[i], d.col_grid[i]});
+    for (int i = 0; i < d.ntile; ++i)
+        if (d.tile_grid[i] > 0) cands.push_back({d.tile_w[i], 0, d.tile_r[i], d.tile_grid[i]});
     for (size_t ci = 0; ok && ci < cands.size(); ++ci) {
         const int w = cands[ci].w;
-        if (!(ok = use_table(w))) break;
+        if (!(ok = use_table(w, cands[ci].relay))) break;
         for (int f = 4; ok && f >= 2; --f) {
             const SolveArgs<T> c = shape_args(w, std::max(1, cands[ci].grid * f / 4), cands[ci].xcd, cands[ci].relay);
             launch_m2d<T>(a, g, s);
@@ -968,11 +1048,12 @@ void tune_sweep(dsn_problem *p, SolveArgs<T> &a, int g, hipStream_t s)
     d.xcd_use = best.xcd;
     d.relay = best.relay;
     d.sweep_nitems = sweep_items(p, d.wpb, d.relay);
-    ds = diagonal_starts(p, S, d.wpb);
+    ds = diagonal_starts(p, S, d.wpb, d.relay);
     (void)hipMemcpyAsync(d.sweep_dstart, ds.data(), ds.size() * sizeof(int), hipMemcpyHostToDevice, s);
     (void)hipStreamSynchronize(s);
     d.dstart_S = S;
     d.dstart_wpb = d.wpb;
+    d.dstart_relay = d.relay;
     a.sweep_wpb = d.wpb;
     a.sweep_grid = d.sweep_grid;
     a.sweep_xcd = d.xcd_use;
@@ -1193,7 +1274,6 @@ dsn_status solve_sources(dsn_problem *p, const dsn_source *src, int32_t n_src, c
 // solve.  Results equal those of the problems solved one by one (the same
 // kernels and arithmetic; the launch shape changes no result).
 // ---------------------------------------------------------------------------
-constexpr int kFacesFused = 9;  // face words written by a fused batch (the next single sweep invalidates them)
 
 // Why a fused batch cannot run these problems ("" if it can).
 std::string fused_obstacle(dsn_problem *const *probs, int32_t n_probs, const int32_t *n_src)
@@ -1878,27 +1958,23 @@ dsn_status solve_noalloc(dsn_problem *p, const dsn_source &src, const dsn_solve_
     // the handle's launch shape when it has one on the global queue, else
     // the default shape (the sizes do not depend on the shape)
     const DeviceState &d = p->dev;
-    int wpb = sweep_wpb(p->D, fp64), grid = 0, relay = 0;
-    if (d.ready && d.tuned && d.xcd_use == 0) {
-        wpb = d.wpb;
-        grid = d.sweep_grid;
-        relay = d.relay;
-    }
+    unsigned char *base = nullptr;
+    int n_cu = 0;
+    const bool own = d.ready && d.tuned && d.xcd_use == 0;
     uint8_t *mat_nat = nullptr;
     double *dens_nat = nullptr;
     Carve count{nullptr};
-    (void)carve_args<T>(p, count, wpb, relay, 1, &mat_nat, &dens_nat);
+    (void)carve_args<T>(p, count, 1, 0, 1, &mat_nat, &dens_nat);
     if (count.off > kScratchBytes)
         return fail(DSN_ERR_UNSUPPORTED, "dsn_solve_noalloc: the solve needs " + std::to_string(count.off) +
                                              " bytes of device memory, above its fixed maximum of " +
                                              std::to_string(kScratchBytes));
-    if ((double)sweep_items(p, wpb, relay) >= (double)(1 << 29))
+    if ((double)sweep_items(p, 1) >= (double)(1 << 29))
         return fail(DSN_ERR_UNSUPPORTED, "too many sweep items (directions x pencils)");
-    unsigned char *base = nullptr;
-    int n_cu = 0;
     dsn_status st = scratch_of(&base, &n_cu);
     if (st != DSN_OK) return st;
-    if (grid < 1) grid = sweep_grid<T>(wpb, p->fixup, n_cu);
+    const SweepShape shape = own ? SweepShape{d.wpb, d.sweep_grid, 0, 0.f, d.relay} : default_shape(p, 1, n_cu, 0.0);
+    const int wpb = shape.wpb, grid = shape.blocks, relay = shape.relay;
     if (grid < 1) return fail(DSN_ERR_UNSUPPORTED, "no sweep kernel of this shape fits the device");
     Carve c{base};
     SolveArgs<T> a = carve_args<T>(p, c, wpb, relay, grid, &mat_nat, &dens_nat);
@@ -1929,17 +2005,7 @@ dsn_status solve_noalloc(dsn_problem *p, const dsn_source &src, const dsn_solve_
         for (int t = 0; t < 3; ++t) par[8 + t] = nrm[t] / std::sqrt(l2);
         par[11] = std::sin(src.fan_half_thickness);
     }
-    {
-        // the diagonal table of the sweep's tickets (one source)
-        const int NJ = gm.NJ, NK = gm.NK, ngrp = p->D / wpb;
-        int *ds = p->dstart_host.data();
-        ds[0] = 0;
-        for (int dd = 0; dd <= NJ + NK - 2; ++dd) {
-            const int lo = std::max(0, dd - (NK - 1)), hi = std::min(dd, NJ - 1);
-            ds[dd + 1] = ds[dd] + (hi - lo + 1) * 8 * ngrp;
-        }
-        ds[NJ + NK] = ds[NJ + NK - 1];
-    }
+    diagonal_starts(item_grid(p, wpb, relay), 1, p->dstart_host.data());  // the sweep's tickets (one source)
     DSN_HIP(hipMemcpyAsync(mat_nat, p->material.data(), (size_t)gm.V, hipMemcpyHostToDevice, s));
     if (dens_nat)
         DSN_HIP(hipMemcpyAsync(dens_nat, p->density.data(), (size_t)gm.V * sizeof(double), hipMemcpyHostToDevice, s));
@@ -2058,21 +2124,20 @@ dsn_status dsn_set_sweep_shape(dsn_problem *p, int32_t waves_per_block, int32_t 
         if (xcd_queues < 0) return fail(DSN_ERR_INVALID_ARG, "xcd_queues must be >= 0");
         if (relay < 0) return fail(DSN_ERR_INVALID_ARG, "relay must be >= 0");
         if (relay > 0 && xcd_queues > 0)
-            return fail(DSN_ERR_INVALID_ARG, "column-relay sweeps use the global ticket queue (xcd_queues 0)");
+            return fail(DSN_ERR_INVALID_ARG, "tile sweeps use the global ticket queue (xcd_queues 0)");
         if (relay > 0) {
-            int cw[kMaxCol], cr[kMaxCol];
-            const int nc = sweep_col_choices(fp64, cw, cr);
-            bool col_built = false;
-            for (int i = 0; i < nc; ++i) col_built = col_built || (cw[i] == w && cr[i] == relay);
-            if (!col_built)
-                return fail(DSN_ERR_INVALID_ARG, "(waves_per_block, relay) is not a built column-relay shape");
+            int cw[kMaxTile], cr[kMaxTile];
+            const int nc = sweep_tile_choices(fp64, cw, cr);
+            bool tile_built = false;
+            for (int i = 0; i < nc; ++i) tile_built = tile_built || (cw[i] == w && cr[i] == relay);
+            if (!tile_built) return fail(DSN_ERR_INVALID_ARG, "(waves_per_block, relay) is not a built tile shape");
         }
         dsn_status st = ensure_device(p);
         if (st != DSN_OK) return st;
         DeviceState &d = p->dev;
         if (d.grid_of[w] < 1) return fail(DSN_ERR_UNSUPPORTED, "no sweep kernel of that shape fits the device");
-        if (relay > 0 && col_grid_of(d, w, relay) < 1)
-            return fail(DSN_ERR_UNSUPPORTED, "the column-relay sweep's LDS does not fit for this x extent");
+        if (relay > 0 && tile_grid_of(d, w, relay) < 1)
+            return fail(DSN_ERR_UNSUPPORTED, "the tile shape is not built for this x extent");
         if (xcd_queues != 0) {
             if (xcd_queues != d.xcd_nq || !sweep_xcd_supported(fp64, p->fixup, w))
                 return fail(DSN_ERR_UNSUPPORTED, "per-XCD queues: FP32 with the fixup, waves_per_block <= 4, and "
@@ -2266,6 +2331,7 @@ dsn_status dsn_solve(dsn_problem *p, const dsn_source *src, int32_t n_src, const
         if (n_src == 0) return DSN_OK;
         if ((st = ensure_device(p)) != DSN_OK) return st;
         hipStream_t s = (hipStream_t)opts->stream;
+        p->dev.rounds_beside = 0.0;
         StageTimer &tm = p->dev.timer;
         tm.on = opts->profile != 0;
         tm.s = s;
@@ -2342,6 +2408,7 @@ dsn_status dsn_solve_adjoint(dsn_problem *p, const dsn_source *src, const double
         if ((st = ensure_device(p)) != DSN_OK) return st;
         if ((st = ensure_adjoint(p)) != DSN_OK) return st;
         hipStream_t s = (hipStream_t)opts->stream;
+        p->dev.rounds_beside = 0.0;
         p->dev.timer.on = false;
         if (info) {
             info->updates = 0;
@@ -2495,6 +2562,12 @@ dsn_status dsn_solve_batch(dsn_problem *const *probs, int32_t n_probs, const dsn
             const dsn_status st = joint_batch_limits(probs, n_probs, n_src, per_batch);
             if (st != DSN_OK) return st;
         }
+        double rounds = 0.0;
+        for (int b = 0; b < n_probs; ++b)
+            if (n_src[b] > 0) rounds += sweep_rounds(probs[b], per_batch[b], probs[b]->dev.n_cu);
+        for (int b = 0; b < n_probs; ++b)
+            if (n_src[b] > 0)
+                probs[b]->dev.rounds_beside = rounds - sweep_rounds(probs[b], per_batch[b], probs[b]->dev.n_cu);
         std::vector<Job> jobs(n_probs);
         std::vector<std::thread> workers;
         struct JoinAll {  // joins the started workers on every way out, exceptions included

@@ -80,9 +80,18 @@ __device__ __forceinline__ double fmin3(double a, double b, double c) { return f
 //            by 2 / c_a)
 constexpr int kDD = 0, kFixup = 1, kRecord = 2, kTrans = 3;
 
-template <typename T, int MODE>
+// z_ready(oz) is called with every value of the z outflow, the last one final:
+// the tile sweep starts its move to the neighbour lane there, before the fixup's
+// test (the move is on the step's critical path, and the fixup is rare).
+struct NoHook {
+    template <typename T>
+    __device__ void operator()(T) const
+    {
+    }
+};
+template <typename T, int MODE, typename Z = NoHook>
 __device__ __forceinline__ T dd_update(T q, T sg, T cx, T cy, T cz, T csum, T px, T iny, T inz, T &ox_, T &oy_,
-                                       T &oz_, unsigned &mk)
+                                       T &oz_, unsigned &mk, Z z_ready = Z())
 {
     if constexpr (MODE == kTrans) {
         const T kx = (mk & 1u) ? T(0) : T(1), ky = (mk & 2u) ? T(0) : T(1), kz = (mk & 4u) ? T(0) : T(1);
@@ -90,6 +99,7 @@ __device__ __forceinline__ T dd_update(T q, T sg, T cx, T cy, T cz, T csum, T px
         ox_ = (mk & 1u) ? p : T(2) * p - px;
         oy_ = (mk & 2u) ? p : T(2) * p - iny;
         oz_ = (mk & 4u) ? p : T(2) * p - inz;
+        z_ready(oz_);
         return p;
     }
     const T num0 = q + cx * px + cy * iny + cz * inz, den0 = sg + csum;
@@ -97,6 +107,7 @@ __device__ __forceinline__ T dd_update(T q, T sg, T cx, T cy, T cz, T csum, T px
     ox_ = T(2) * p - px;
     oy_ = T(2) * p - iny;
     oz_ = T(2) * p - inz;
+    z_ready(oz_);
     if constexpr (MODE == kFixup || MODE == kRecord) {
         // Set-to-zero fixup.  An axis whose outflow is negative is fixed
         // (m_a = 1): its outflow becomes zero, its inflow enters the balance
@@ -106,6 +117,8 @@ __device__ __forceinline__ T dd_update(T q, T sg, T cx, T cy, T cz, T csum, T px
         // negative reproduces that lane's values exactly, so the passes run
         // branch-free over the whole wave while any lane still needs one.
         T lo = fmin3(ox_, oy_, oz_);
+        // (out of line: most steps fix nothing, and a taken branch over the
+        // passes costs a step an instruction fetch)
         if (__any(lo < T(0))) {
             T mx = T(0), my = T(0), mz = T(0);
             const T hx = T(0.5) * cx * px, hy = T(0.5) * cy * iny, hz = T(0.5) * cz * inz;
@@ -126,9 +139,20 @@ __device__ __forceinline__ T dd_update(T q, T sg, T cx, T cy, T cz, T csum, T px
             }
             if constexpr (MODE == kRecord)
                 mk = (mx != T(0) ? 1u : 0u) | (my != T(0) ? 2u : 0u) | (mz != T(0) ? 4u : 0u);
+            z_ready(oz_);
         }
     }
     return p;
+}
+
+// Values that no kernel writes while a sweep runs, read through the constant
+// address space: uniform ones become scalar loads, which the waves of a CU
+// share through the scalar cache.  As vector loads of a few shared lines by
+// every wave of a launch they took 10 us to come back.
+template <typename X>
+__device__ __forceinline__ X const_load(const X *p)
+{
+    return *(const __attribute__((address_space(4))) X *)p;
 }
 
 // Device-coherent (agent scope) loads and stores: they bypass the per-XCD
@@ -153,6 +177,7 @@ __device__ __forceinline__ void coherent_store(T *p, T v)
 // loads it needs, never for the completion of earlier stores.
 typedef __amdgpu_buffer_rsrc_t Rsrc;
 typedef __attribute__((ext_vector_type(2))) unsigned U32x2;
+typedef __attribute__((ext_vector_type(4))) unsigned U4;
 constexpr int kDstLds = 256;            // diagonal-start table entries kept in LDS
 constexpr int kSigTab = 32;             // per-block sigma table: materials < kMaxMat, the ghost byte 255 -> 31
 static_assert(kMaxMat <= 16, "the ghost byte must land on a zero entry of the sigma table");
@@ -168,6 +193,17 @@ constexpr int kQueueCtr = 4;             // first per-XCD ticket counter in the 
 __device__ __forceinline__ Rsrc make_rsrc(const void *base, unsigned bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, kRawDword3);
+}
+// The same, for an address that is the same in every lane of a wave but that
+// the compiler cannot prove to be (else it would loop over the lanes' values
+// around every access).
+__device__ __forceinline__ Rsrc make_uniform_rsrc(const void *base, unsigned bytes)
+{
+    const unsigned long long p = (unsigned long long)base;
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)p);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(p >> 32));
+    return make_rsrc((const void *)((unsigned long long)hi << 32 | lo),
+                     (unsigned)__builtin_amdgcn_readfirstlane((int)bytes));
 }
 template <int AUX = 0>
 __device__ __forceinline__ float buf_load(Rsrc r, unsigned off, float)
@@ -780,315 +816,453 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(sizeof
     sweep_body<T, MODE, WPB, SM, false, NT, true>(a0, g);
 }
 
-// Column-relay sweep: the same cell updates as k_sweep with the y faces
-// kept on chip.
+// Tile sweep: the same cell updates as k_sweep with the faces between the
+// pencils of a tile kept on chip.
 //
-// Work item = (octant o, group of W directions dg, pencil row K_r,
-// source): every pencil (J_r, K_r), J_r = 0 .. NJ-1, of W directions.  The
-// block has W x R waves; wave (slot, role) sweeps direction dg * W + slot
-// over the pencils J_r = role, role + R, role + 2R, ... in turn, each with
-// the per-wave pipeline of k_sweep (LDS row ring, skewed face rings, chunks
-// of 8 steps).  The y outflow of pencil J_r is the y inflow of pencil
-// J_r + 1, which the wave of the next role sweeps: it is handed over in LDS
-// (a buffer of one pencil's face rows per wave, with counters of the rows
-// published and consumed), so y faces never reach memory.  Only the z faces
-// between rows K_r - 1 and K_r go through the stamped face words of k_sweep.
-// The handover waits are bounded like the face-word polls.
+// Work item = (octant o, direction, tile (TJ_r, TK_r) of tile_y x tile_z
+// pencils, source), swept by a team of tile_y * tile_z waves of one block, one
+// pencil each, with the per-wave pipeline of k_sweep.  A pencil's y and z
+// outflow is handed to the team's next pencil in LDS; only the faces on the
+// rim of the tile go through the stamped face words.  What bounds the sweep
+// of a small mesh is the chain of pencils along a diagonal: through memory a
+// downstream pencil starts three 8-step chunks plus a store-to-load trip of
+// 1-2 us after its upstream one.  In LDS the trip is gone, and the hop is 15
+// steps: a lane needs the upstream lane's outflow of seven steps later
+// (skews 7 apart, same row), so when a pencil's chunk grid is shifted by one
+// step against its upstream neighbour's - the phase p = -(J_r + K_r) mod 8,
+// p idle steps before the first row - the outflow of one upstream chunk is
+// exactly the inflow of one downstream chunk.  Face values are therefore
+// exchanged by step, not by row: ring entry (b, e) of a chunk is what the
+// lane of entry e made at the chunk's step b, which is what the downstream
+// lane of that entry needs at its own step b.
 //
-// Tickets are numbered row by row (all items of K_r = 0 first), so an
-// item's upstream item (K_r - 1) holds a smaller ticket and is already
-// running: every wait ends.  Inside a block the waits point to smaller J_r
-// only (the inflow of J_r comes from J_r - 1; a wave re-fills its handover
-// buffer with pencil J_r + R only after J_r + 1 has read those rows).
-template <typename T, int MODE, int W, int R, bool SM, bool NT>
-__global__ __launch_bounds__(64 * W * R) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) void k_sweep_col(SolveArgs<T> a0, int g)
+// The teams' waves run free: each takes the team's items in order from a
+// small ring of tickets (the leading wave fetches them), starts its pencil as
+// soon as its inflow is there and goes straight on to the next item, so a
+// team pipelines from item to item with no barrier.  Per link and wave a
+// counter of the chunks handed over and one of the chunks consumed (kept for
+// the whole launch) order the ring of kTileSlots chunks; one LDS read per
+// chunk checks both inflows and both outflow rings.
+//
+// Tickets go tile diagonal by tile diagonal, so an item's upstream tiles hold
+// smaller tickets.  Inside a team a wave waits for its upstream waves' next
+// chunk of the same or an earlier item, or for a downstream wave to consume a
+// chunk at least kTileSlots behind; in the order (item, chunk + j + k) both
+// are smaller, so every wait ends.  All are bounded as in k_sweep.
+//
+// Global rim words: word (slot, entry) of a pencil face, slot = u mod nx with
+// u = row + the entry's skew along the face: a bijection of the nx rows of
+// each entry, and a chunk's words are one contiguous run (split where it
+// wraps).
+constexpr int kTileSlots = 3;  // chunks a handover ring holds: 2 stall on jitter, 4 do not fit 16 FP32 waves
+constexpr int kItemRing = 8;   // tickets the leading wave may be ahead of the team's last wave
+
+template <typename T, int MODE, int NW, bool SM, bool NT>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : NW > 8 ? 4 : 3))) void k_sweep_tile(SolveArgs<T> a0, int g)
 {
-    static_assert(MODE == kDD || MODE == kFixup, "forward cell modes only");
-    constexpr int kLoadAux = kSC1, kPollAux = kVolatileSC1, kStoreAux = kSC1;
     constexpr int kPsiAux = NT ? kNT : 0;
     typedef SigSrc<T, SM> Sig;
     typedef typename FaceCodecSel<T, MODE, false>::type Face;
     constexpr bool kSignFace = std::is_same<Face, SignFace<T>>::value;
-    constexpr int NW = W * R;
-    constexpr int RQ = 24, RF = 16, CH = 8;
+    constexpr int RQ = 24, CH = 8, NS = kTileSlots;
     constexpr int RB = 64 * sizeof(T);
     constexpr int FB = 8 * (int)Face::BYTES;
-    __shared__ T sQ[NW][RQ][64];
-    __shared__ T sFYi[NW][RF][8], sFZi[NW][RF][8], sFYo[NW][RF][8], sFZo[NW][RF][8];
-    __shared__ int sTicket, sNext, sAbort;
-    __shared__ int sProd[NW], sCons[NW];  // handover rows published / consumed (counted over the wave's pencils)
-    __shared__ T sSigT[SM ? kSigTab : 1];
+    constexpr unsigned kNone = 0x80000000u;  // an offset outside every buffer
+    // psi rows move 16 bytes a lane: LR lanes a row, RI rows an access
+    constexpr int LR = RB / 16, RI = 64 / LR, NI = CH / RI, VL = 16 / (int)sizeof(T);
+    __shared__ __align__(16) T sQ[NW][RQ][64];
+    __shared__ __align__(16) T sF[NW][2 + 2 * NS][8][CH];  // face chunks [entry][step]: y, z inflow from memory; y, z outflow rings
     __shared__ __align__(16) unsigned char sMt[SM ? NW : 1][SM ? RQ : 1][64];  // SM: material byte ring (slots as sQ)
-    extern __shared__ unsigned char sDyn[];  // handover buffers [NW][nx][8] of T
-    T *const sRelay = (T *)sDyn;
+    __shared__ int sCtr[NW][4];  // per wave: y, z chunks handed over; y, z chunks its downstream waves have consumed
+    __shared__ int sItem[NW][kItemRing], sPub[NW], sTaken[NW];  // tickets of the team led by the wave; items taken
+    __shared__ int sAbort;
+    __shared__ T sSigT[SM ? kSigTab : 1];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int slot = w / R, role = w % R;
-    const int D = a0.D, ngrp = D / W;
+    const int TY = a0.tile_y, TZ = a0.tile_z, TW = TY * TZ;
+    const int team = w / TW, tw = w - team * TW, lead = team * TW;
+    const int ja = tw % TY, ka = tw / TY;
+    const int D = a0.D;
     const int NJ = a0.g.NJ, NK = a0.g.NK, nx = a0.g.nx;
+    const int NTJ = (NJ + TY - 1) / TY, NTK = (NK + TZ - 1) / TZ;
     int *const ctr = a0.sweep_ctr;
-    const unsigned epoch = (unsigned)ctr[2];
+    // Everything the first item needs that does not depend on its ticket is
+    // asked for together with the ticket: these loads miss every cache, and
+    // one after the other they cost a small mesh more than its steps.  (A
+    // launch with nothing to do leaves the ticket unused; the next launch
+    // starts from zero.)
+    int tnext = 0;
+    bool have_next = false;
+    // its address is made opaque: the compiler would combine a known-uniform
+    // atomic over the lanes, and wait for it on the spot
+    int opaque0 = 0;
+    asm("" : "+v"(opaque0));
+    if (tw == 0 && lead + TW <= NW) {
+        if (lane == 0) tnext = atomicAdd(&ctr[opaque0], 1);
+        have_next = true;
+    }
+    const bool once = (long)gridDim.x * (NW / TW) >= a0.sweep_nitems;  // every item is a team's first
+    const unsigned epoch = (unsigned)const_load(&ctr[2]), par0 = kSignFace ? (unsigned)const_load(a0.face_par) : 0u;
     const int nitems = a0.sweep_nitems;
-    const int per_row = a0.S * 8 * ngrp;  // items of one pencil row K_r
-
+    const int ndiag = NTJ + NTK - 1;
+    const bool dst_reg = ndiag <= 64;  // lane l holds the first ticket of tile diagonal l
+    const int dst = dst_reg && lane < ndiag ? a0.sweep_dstart[lane] : 0;
+    double sig_m = 0.0;
+    if (SM && (int)threadIdx.x < a0.nmat) sig_m = a0.xs_t[threadIdx.x * a0.G + g];
     bool live = false;
-    for (int s = 0; s < a0.S; ++s) live = live || !a0.ctl[(long)s * a0.G + g].done;
+    for (int s = 0; s < a0.S; ++s) live = live || !const_load(&a0.ctl[(long)s * a0.G + g].done);
     if (!live) return;
-    if (SM)
-        for (int i = threadIdx.x; i < kSigTab; i += 64 * NW)
-            sSigT[i] = i < a0.nmat ? (T)a0.xs_t[i * a0.G + g] : T(0);
-    if (threadIdx.x == 0) sNext = -1;
-    // A wave of the last role takes the next ticket three chunks before its
-    // last pencil ends (the block's last work), so the atomic hides behind
-    // those chunks; a block holds at most two tickets, and the smallest
-    // unfinished ticket is always being worked on.
-    for (;;) {
-        __syncthreads();  // every wave is done with the previous item (and sNext is written)
-        if (threadIdx.x == 0) {
-            sTicket = sNext >= 0 ? sNext : atomicAdd(&ctr[0], 1);
-            sNext = -1;
-            sAbort = 0;
+    if (SM && threadIdx.x < kSigTab) sSigT[threadIdx.x] = (T)sig_m;
+    if (threadIdx.x < 4 * NW) (&sCtr[0][0])[threadIdx.x] = 0;
+    if (threadIdx.x < NW) {
+        sPub[threadIdx.x] = 0;
+        sTaken[threadIdx.x] = 0;
+    }
+    if (threadIdx.x == 0) sAbort = 0;
+    __syncthreads();  // the only barrier
+    if (lead + TW > NW) return;  // waves left over
+
+    // waits on LDS state: polled much faster than a face word in memory
+    const int lds_limit = a0.sweep_spin_limit < 1024 ? a0.sweep_spin_limit
+                          : a0.sweep_spin_limit < (1 << 27) ? a0.sweep_spin_limit * 16 : 0x7FFFFFFF;
+    auto abort_all = [&]() {
+        if (lane == 0) {
+            atomicMax(&ctr[0], kTicketStop);
+            coherent_store(&ctr[1], 1);
+            __hip_atomic_store(&sAbort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        if (threadIdx.x < NW) {
-            sProd[threadIdx.x] = 0;
-            sCons[threadIdx.x] = 0;
+    };
+    auto lds_get = [&](const int *x) { return __hip_atomic_load(x, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP); };
+    // past the limit, or another wave (or another block) gave up
+    auto gave_up = [&](int spins, int limit) {
+        return spins > limit ||
+               ((spins & 63) == 0 && __builtin_amdgcn_readfirstlane(__hip_atomic_load(&sAbort, __ATOMIC_RELAXED,
+                                                                                      __HIP_MEMORY_SCOPE_WORKGROUP))) ||
+               ((spins & 255) == 0 && __builtin_amdgcn_readfirstlane(coherent_load(&ctr[1])));
+    };
+    // This wave's links, one lane each: lanes 0 and 1 count the chunks handed
+    // over to y and z and watch their consumption, lanes 2 and 3 count the
+    // chunks consumed from the upstream y and z waves and watch what those hand
+    // over.  (The other lanes repeat lane 0 and pass.)
+    const int wy = ja > 0 ? w - 1 : w, wz = ka > 0 ? w - TY : w;
+    int *const own = &sCtr[0][0] + 4 * w, *const upy = &sCtr[0][0] + 4 * wy, *const upz = &sCtr[0][0] + 4 * wz;
+    int *const watch = lane == 1 ? own + 3 : lane == 2 ? upy : lane == 3 ? upz + 1 : own + 2;
+    int *const tell = lane == 1 ? own + 1 : lane == 2 ? upy + 2 : lane == 3 ? upz + 3 : own;
+    const bool tells = lane < 2 || (lane == 2 && ja > 0) || (lane == 3 && ka > 0);
+    const bool inY = ja > 0, inZ = ka > 0;  // inflow from the team's neighbour (a link)
+    int done = 0;
+    int spy = 0, spz = 0, scy = 0, scz = 0;  // the next ring slots
+    const int jr = lane & 7, kr = lane >> 3;
+    const int skew = jr + kr;
+    const int srcZ = ((lane - 8) & 63) << 2;
+    const bool yb = jr == 0, zb = kr == 0, yo = jr == 7, zo = kr == 7;
+    const int e = lane & 7, ro = lane >> 3;
+    const int lrow = lane / LR, lcol = lane % LR;
+
+    bool good = true;
+    for (int seq = 0; good; ++seq) {
+        int t = 0;
+        if (tw == 0) {
+            if (seq >= kItemRing) {  // the ring's oldest ticket must have been taken by every wave
+                int spins = 0;
+                while (good && __any(lane >= 1 && lane < TW && lds_get(&sTaken[lead + (lane < TW ? lane : 0)]) <= seq - kItemRing)) {
+                    __builtin_amdgcn_s_sleep(1);
+                    good = !gave_up(++spins, lds_limit);
+                }
+            }
+            if (lane == 0) {
+                t = have_next ? tnext : once ? nitems : atomicAdd(&ctr[opaque0], 1);
+                sItem[lead][seq & (kItemRing - 1)] = t;
+                __hip_atomic_store(&sPub[lead], seq + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            have_next = false;
+            t = __builtin_amdgcn_readfirstlane(t);
+        } else {
+            int spins = 0;
+            while (good && __builtin_amdgcn_readfirstlane(lds_get(&sPub[lead])) <= seq) {
+                __builtin_amdgcn_s_sleep(1);
+                good = !gave_up(++spins, lds_limit);
+            }
+            t = __builtin_amdgcn_readfirstlane(sItem[lead][seq & (kItemRing - 1)]);
+            if (lane == 0) __hip_atomic_store(&sTaken[w], seq + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        __syncthreads();
-        const int t = __builtin_amdgcn_readfirstlane(sTicket);
-        if (t >= nitems) break;
-        const int Kr = t / per_row;
-        int u = t - Kr * per_row;
-        const int dg = u % ngrp;
-        u /= ngrp;
+        if (!good || t >= nitems) break;
+        // ticket -> (tile diagonal, position, direction, octant, source)
+        int d = 0;
+        if (dst_reg) {
+            d = __popcll(__ballot(lane >= 1 && lane < ndiag && dst <= t));
+        } else {
+            int hi = ndiag - 1;
+            while (d < hi) {
+                const int mid = (d + hi + 1) >> 1;
+                if (const_load(&a0.sweep_dstart[mid]) <= t) d = mid;
+                else hi = mid - 1;
+            }
+        }
+        int u = t - (dst_reg ? __builtin_amdgcn_readlane(dst, d) : const_load(&a0.sweep_dstart[d]));
+        const int Tlo = d - (NTK - 1) > 0 ? d - (NTK - 1) : 0;
+        const int Thi = d < NTJ - 1 ? d : NTJ - 1;
+        const int P = Thi - Tlo + 1;
+        const int TJ = Tlo + u % P;
+        u /= P;
+        const int dir = u % D;
+        u /= D;
         const int o = u & 7, src = u >> 3;
+        const int Jr = TJ * TY + ja, Kr = (d - TJ) * TZ + ka;
+        if (Jr >= NJ || Kr >= NK) continue;  // a pencil outside the mesh (its links are off)
         const SolveArgs<T> a = at_source(a0, src);
-        if (a.ctl[g].done) continue;  // this source's group has converged
-        const int n = o * D + dg * W + slot;
-        const unsigned stamp = kSignFace ? (unsigned)a.face_par[0] : epoch;
-        const int sx = (o & 1) ? -1 : 1, sy = (o & 2) ? -1 : 1, sz = (o & 4) ? -1 : 1;
-        const int K = sz > 0 ? Kr : NK - 1 - Kr;
-        const int jr = lane & 7, kr = lane >> 3;
+        if (a0.S > 1 && const_load(&a.ctl[g].done)) continue;  // this source's group has converged
+        const int n = o * D + dir;
+        const unsigned stamp = kSignFace ? (a0.S > 1 ? (unsigned)const_load(a.face_par) : par0) : epoch;
+        const int og = a.rev ? (o ^ 7) : o;
+        const int sx = (og & 1) ? -1 : 1, sy = (og & 2) ? -1 : 1, sz = (og & 4) ? -1 : 1;
+        const int J = sy > 0 ? Jr : NJ - 1 - Jr, K = sz > 0 ? Kr : NK - 1 - Kr;
         const int jp = sy > 0 ? jr : 7 - jr, kp = sz > 0 ? kr : 7 - kr;
         const int pl = jp + 8 * kp;
-        const int skew = jr + kr;
-        const int srcZ = ((lane - 8) & 63) << 2;
-        const bool yb = jr == 0, zb = kr == 0, yo = jr == 7, zo = kr == 7;
-        const T cx = a.cdir[3 * n], cy = a.cdir[3 * n + 1], cz = a.cdir[3 * n + 2];
+        const T cx = const_load(&a.cdir[3 * n]), cy = const_load(&a.cdir[3 * n + 1]), cz = const_load(&a.cdir[3 * n + 2]);
         const T csum = cx + cy + cz;
-        constexpr int FU = Face::BYTES / 4;
-        unsigned *const fZ = (unsigned *)a.faceZ;
-        const long fdir = (long)n * NJ * NK * nx * 8 * FU;
-        const bool hasZ = Kr > 0;
-        const unsigned fbytes = (unsigned)(nx * FB);
-        const int pstep = sx * RB, pbase = sx > 0 ? 0 : (nx - 1) * RB;
-        const int fstep = sx * FB, fbase = sx > 0 ? 0 : (nx - 1) * FB;
-        const int lofs = lane * (int)sizeof(T);
-        const int e = lane & 7, ro = lane >> 3;
+        const long pen = (long)K * NJ + J;
+        const Rsrc rPsi = make_uniform_rsrc(a.psi + psi_run(pen, a.Nd, n, nx), (unsigned)(nx * RB));
+        const Rsrc rSig = SM ? make_uniform_rsrc(a.mat + pen * nx * 64, (unsigned)(nx * 64))
+                             : make_uniform_rsrc(a.sig + pen * nx * 64, (unsigned)(nx * RB));
+        constexpr bool kMask = MODE == kRecord || MODE == kTrans;
+        const Rsrc rMask = make_uniform_rsrc(kMask ? a.mask + (long)n * a.g.Vp + pen * nx * 64 : a.mat,
+                                     kMask ? (unsigned)(nx * 64) : 0u);
+        const int mbase = sx > 0 ? 0 : (nx - 1) * 64, mstep = sx * 64;
+        // Face words in memory: in from the upstream pencil, out in this
+        // pencil's own.  One buffer per axis spans both (the lower pencil
+        // first); no face (the mesh boundary, or a link) = offset kNone.
+        const bool gY = !inY && Jr > 0, gZ = !inZ && Kr > 0;
+        const bool outY = ja < TY - 1 && Jr < NJ - 1, outZ = ka < TZ - 1 && Kr < NK - 1;
+        const unsigned fpen = (unsigned)(nx * FB);  // bytes of a pencil face
+        const long fdir = (long)n * NJ * NK;        // pencil faces before this direction's
+        const Rsrc rFY = make_uniform_rsrc((char *)a.faceY + (fdir + pen - (Jr > 0 && sy > 0 ? 1 : 0)) * fpen,
+                                   Jr > 0 ? 2 * fpen : fpen);
+        const Rsrc rFZ = make_uniform_rsrc((char *)a.faceZ + (fdir + pen - (Kr > 0 && sz > 0 ? NJ : 0)) * fpen,
+                                   Kr > 0 ? (unsigned)(NJ + 1) * fpen : fpen);
+        const unsigned inYo = sy > 0 ? 0u : fpen, ownYo = Jr > 0 && sy > 0 ? fpen : 0u;
+        const unsigned inZo = sz > 0 ? 0u : NJ * fpen, ownZo = Kr > 0 && sz > 0 ? NJ * fpen : 0u;
+        // chunk c holds steps 8c - ph .. 8c - ph + 7; ring slots, prologue
+        // rows and the chunk count are those of k_sweep with the ph idle
+        // steps as rows before the first (out of every buffer: zero source
+        // and inflow)
+        const int ph = (-(Jr + Kr)) & 7;
+        const int first_out = ph > 0 ? 1 : 0;  // downstream starts after chunk 0's steps when ph > 0
+        const int phu = (ph + 1) & 7;          // the upstream pencils' phase
+        const int nlink = (nx + phu + 15) / CH + 1 - (phu > 0 ? 1 : 0);  // chunks they hand over
+        const int nchunks = (nx + ph + 15) / CH + 1;
+        const int cnext = nchunks > 3 ? nchunks - 3 : 0;
+        const int pstep = sx * RB;
+        int poff = (sx > 0 ? 0 : (nx - 1) * RB) + (lrow - ph) * pstep + lcol * 16;  // next chunk's rows, this lane
+        // face words: entry e's word of step u (row u - skew) sits in slot
+        // u mod nx; this lane moves step ro of a chunk
         const int skY = sz > 0 ? e : 7 - e, skZ = sy > 0 ? e : 7 - e;
-        const int eoff = e * (int)Face::BYTES;
+        int uin = ro - ph;  // the next chunk's inflow step of this lane
+        const bool pY = !outY && Jr < NJ - 1, pZ = !outZ && Kr < NK - 1;  // outflow to memory
+        auto face_off = [&](int u_, int sk, unsigned base) -> unsigned {
+            int slot = u_ < nx ? u_ : u_ - nx;
+            if (nx < 8) slot = u_ % nx;
+            return (unsigned)(u_ - sk) < (unsigned)nx ? base + (unsigned)(slot * FB + e * (int)Face::BYTES) : kNone;
+        };
         constexpr int SR = Sig::ROW;
-        const int sbase = sx > 0 ? 0 : (nx - 1) * SR, sstep = sx * SR;
-        const int slofs = pl * (SR / 64);
-        const int nchunks = (nx + 15) / CH + 1;
-        // handover buffers: this wave's outflow, and the inflow from the
-        // wave of the previous role (the last role's for role 0, one pencil
-        // behind)
-        const int win = slot * R + (role + R - 1) % R;
-        T *const relOut = sRelay + (long)w * nx * 8;
-        const T *const relIn = sRelay + (long)win * nx * 8;
-        const int npen = role < NJ ? (NJ - 1 - role) / R + 1 : 0;
-        bool good = true;
-        for (int k = 0; k < npen && good; ++k) {
-            const int Jr = role + R * k;
-            const int J = sy > 0 ? Jr : NJ - 1 - Jr;
-            const bool hasY = Jr > 0, needY = Jr < NJ - 1;
-            const int seq_in = role == 0 ? k - 1 : k;  // the inflow's pencil in its producer's order
-            const long pen = (long)K * NJ + J;
-            const Rsrc rPsi = make_rsrc(a.psi + psi_run(pen, a.Nd, n, nx), (unsigned)(nx * RB));
-            const Rsrc rSig = SM ? make_rsrc(a.mat + pen * nx * 64, (unsigned)(nx * 64))
-                                 : make_rsrc(a.sig + pen * nx * 64, (unsigned)(nx * RB));
-            const long fown = fdir + pen * nx * 8 * FU;
-            const Rsrc rFZo = make_rsrc(fZ + fown, Kr < NK - 1 ? fbytes : 0u);  // the last row's are never read
-            const Rsrc rFZi = make_rsrc(fZ + (hasZ ? fdir + ((long)(K - sz) * NJ + J) * nx * 8 * FU : 0),
-                                        hasZ ? fbytes : 0);
-            T pq[CH];
-            U32x2 pmt;                 // SM: material bytes of the next chunk (load phase)
-            typename Sig::Reg ps[CH];  // !SM: sigma of the lane's column at the current chunk's steps
-            typename Face::Word pfz;
-            auto load_rows = [&](int c) {
-                int off = pbase + CH * c * pstep + lofs;
+        const int sstep = sx * SR;
+        // sigma of row + ph = r in the lane's own column
+        auto sig_off = [&](int r) { return (sx > 0 ? 0 : (nx - 1) * SR) + (r - ph) * sstep + pl * (SR / 64); };
+
+        U4 pq[NI];                 // psi rows of the next chunk
+        U32x2 pmt;                 // SM: material bytes of the next chunk
+        typename Sig::Reg ps[CH];  // !SM: sigma of the lane's column at the current chunk's steps
+        unsigned pm[CH];           // kTrans: fixed-axis sets of the lane's cells at the current chunk's steps
+        typename Face::Word pfy, pfz;
+        unsigned offy = kNone, offz = kNone;
+        // rows and inflow words of the next chunk (poff, uin), which starts at row r0
+        auto load_rows = [&](int r0) {
 #pragma unroll
-                for (int b = 0; b < CH; ++b, off += pstep) pq[b] = buf_load<kPsiAux>(rPsi, (unsigned)off, T());
-                const unsigned fo = (unsigned)(fbase + (CH * c + ro) * fstep + eoff);
-                Face::template load<kLoadAux>(pfz, rFZi, fo);
-                if constexpr (SM) pmt = load_mat_rows(rSig, c, sx, nx, lane);
-            };
-            // a bounded wait on a handover counter of this block
-            auto wait_lds = [&](const int *cnt, int need) -> bool {
-                int spins = 0;
-                while (__hip_atomic_load(cnt, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < need) {
-                    __builtin_amdgcn_s_sleep(1);
-                    if (++spins > a0.sweep_spin_limit ||
-                        ((spins & 255) == 0 && (__hip_atomic_load(&sAbort, __ATOMIC_RELAXED,
-                                                                  __HIP_MEMORY_SCOPE_WORKGROUP) ||
-                                                coherent_load(&ctr[1]))))
-                        return false;
-                }
-                return true;
-            };
-            auto abort_all = [&]() {
-                atomicMax(&ctr[0], kTicketStop);
-                coherent_store(&ctr[1], 1);
-                __hip_atomic_store(&sAbort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            };
-            auto commit = [&](int c) -> bool {
-                const int q0 = (CH * c) % RQ;
-#pragma unroll
-                for (int b = 0; b < CH; ++b) sQ[w][q0 + b][lane] = pq[b];
-                if constexpr (SM) *(U32x2 *)&sMt[w][q0 + mat_row(sx, lane)][8 * (lane & 7)] = pmt;
-                const int r = CH * c + ro;
-                const bool valid = r < nx;
-                bool okZ = !valid || !hasZ || Face::ok(pfz, stamp);
-                int spins = 0;
-                if (__any(!okZ)) {
-                    const unsigned fo = (unsigned)(fbase + r * fstep + eoff);
-                    do {
-                        __builtin_amdgcn_s_sleep(2);
-                        if (!okZ) {
-                            Face::template load<kPollAux>(pfz, rFZi, fo);
-                            okZ = Face::ok(pfz, stamp);
-                        }
-                        if (++spins > a0.sweep_spin_limit || ((spins & 255) == 0 && coherent_load(&ctr[1]))) {
-                            abort_all();
-                            return false;
-                        }
-                    } while (__any(!okZ));
-                }
-                sFZi[w][(r + skZ) & (RF - 1)][e] = Face::value(pfz);
-                T fy = T(0);
-                if (hasY) {
-                    const int upto = CH * c + CH < nx ? CH * c + CH : nx;
-                    if (!wait_lds(&sProd[win], seq_in * nx + upto)) {
-                        abort_all();
-                        return false;
-                    }
-                    if (valid) fy = relIn[r * 8 + e];
-                }
-                sFYi[w][(r + skY) & (RF - 1)][e] = fy;
-                if (hasY && lane == 0)  // the rows of this chunk are read: the producer may reuse them
-                    __hip_atomic_store(&sCons[win], seq_in * nx + (CH * c + CH < nx ? CH * c + CH : nx),
-                                       __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                return true;
-            };
-            auto sig_off = [&](int ir0) { return sbase + ir0 * sstep + slofs; };
-            T px = T(0), oy = T(0), oz = T(0);
-            auto steps = [&](int c) {
-                const int t0 = CH * c, ir0 = t0 - skew;
-                int s0 = ir0 % RQ;
-                s0 = s0 < 0 ? s0 + RQ : s0;
-                const int ft = t0 & (RF - 1);
-                int sq[CH];
-                T q[CH], fy[CH], fz[CH], po[CH], yo_[CH], zo_[CH], sg[CH];
-#pragma unroll
-                for (int b = 0; b < CH; ++b) {
-                    sq[b] = s0 + b < RQ ? s0 + b : s0 + b - RQ;
-                    q[b] = sQ[w][sq[b]][pl];
-                    fy[b] = sFYi[w][ft + b][kp];
-                    fz[b] = sFZi[w][ft + b][jp];
-                    if constexpr (SM) sg[b] = sSigT[sMt[w][sq[b]][pl] & (kSigTab - 1)];
-                }
-                int so = sig_off(ir0 + CH);
-#pragma unroll
-                for (int b = 0; b < CH; ++b, so += sstep) {
-                    T iny = lane_shr1(oy);
-                    T inz = lane_from(oz, srcZ);
-                    iny = yb ? fy[b] : iny;
-                    inz = zb ? fz[b] : inz;
-                    T ox_, oy_, oz_;
-                    unsigned mk = 0;
-                    if constexpr (!SM) sg[b] = Sig::value(ps[b], sSigT);
-                    po[b] = dd_update<T, MODE>(q[b], sg[b], cx, cy, cz, csum, px, iny, inz, ox_, oy_, oz_, mk);
-                    yo_[b] = oy_;
-                    zo_[b] = oz_;
-                    px = ox_;
-                    oy = oy_;
-                    oz = oz_;
-                    if constexpr (!SM) ps[b] = Sig::load(rSig, (unsigned)so);
-                }
-#pragma unroll
-                for (int b = 0; b < CH; ++b) sQ[w][sq[b]][pl] = po[b];
-                if (yo) {
-#pragma unroll
-                    for (int b = 0; b < CH; ++b) sFYo[w][ft + b][kp] = yo_[b];
-                }
-                if (zo) {
-#pragma unroll
-                    for (int b = 0; b < CH; ++b) sFZo[w][ft + b][jp] = zo_[b];
-                }
-            };
-            auto writeback = [&](int c) -> bool {
-                const int qw = (CH * c + CH) % RQ;
-                T v[CH];
-#pragma unroll
-                for (int b = 0; b < CH; ++b) v[b] = sQ[w][qw + b][lane];
-                int off = pbase + (CH * c - 16) * pstep + lofs;
-#pragma unroll
-                for (int b = 0; b < CH; ++b, off += pstep) buf_store<kPsiAux>(rPsi, (unsigned)off, v[b]);
-                const int r = CH * c - 14 + ro;
-                const unsigned fo = (unsigned)(fbase + r * fstep + eoff);
-                Face::template put<kStoreAux>(rFZo, fo, sFZo[w][(r + 7 + skZ) & (RF - 1)][e], stamp);
-                if (needY) {
-                    // rows CH c - 14 .. CH c - 7 are complete; before they
-                    // overwrite the previous pencil's, its reader must be done
-                    // with them
-                    const int hi = CH * c - 6 < nx ? CH * c - 6 : nx;
-                    if (hi > 0) {
-                        if (k > 0 && !wait_lds(&sCons[w], (k - 1) * nx + hi)) {
-                            abort_all();
-                            return false;
-                        }
-                        if (r >= 0 && r < nx) relOut[r * 8 + e] = sFYo[w][(r + 7 + skY) & (RF - 1)][e];
-                        if (lane == 0)
-                            __hip_atomic_store(&sProd[w], k * nx + hi, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    }
-                }
-                return true;
-            };
-            const int cnext = nchunks > 3 ? nchunks - 3 : 0;
-#pragma unroll
-            for (int s = RQ - 14; s < RQ; ++s) sQ[w][s][lane] = T(0);
+            for (int i = 0; i < NI; ++i)
+                pq[i] = __builtin_amdgcn_raw_buffer_load_b128(rPsi, (unsigned)(poff + i * RI * pstep), 0, kPsiAux);
+            if (gY) offy = face_off(uin, skY, inYo);
+            if (gZ) offz = face_off(uin, skZ, inZo);
+            Face::template load<kSC1>(pfy, rFY, offy);
+            Face::template load<kSC1>(pfz, rFZ, offz);
             if constexpr (SM) {
-#pragma unroll
-                for (int s = RQ - 14; s < RQ; ++s) sMt[w][s][lane] = 255;  // the ghost: zero sigma
+                const int row0 = sx > 0 ? r0 : nx - 8 - r0;
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(rSig, (unsigned)(row0 * 64 + 8 * lane), 0, 0);
+                pmt = U32x2{v[0], v[1]};
             }
-            sFYi[w][lane >> 2][(lane & 3) * 2] = T(0);
-            sFYi[w][lane >> 2][(lane & 3) * 2 + 1] = T(0);
-            sFZi[w][lane >> 2][(lane & 3) * 2] = T(0);
-            sFZi[w][lane >> 2][(lane & 3) * 2 + 1] = T(0);
-            load_rows(0);
-            __builtin_amdgcn_sched_barrier(0);
+        };
+        // the outflow words of one chunk (dropped off the tile's rim): what
+        // its step b made is used downstream at step b - 7
+        auto put_faces = [&](int uo) {
+            unsigned oy_ = kNone, oz_ = kNone;
+            if (pY) oy_ = face_off(uo, skY, ownYo);
+            if (pZ) oz_ = face_off(uo, skZ, ownZo);
+            Face::template put<kSC1>(rFY, oy_, sF[w][2 + spy][e][ro], stamp);
+            Face::template put<kSC1>(rFZ, oz_, sF[w][2 + NS + spz][e][ro], stamp);
+        };
+        // psi rows of the ring from slot qw on, of the chunk three before poff
+        auto put_rows = [&](int qw) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+                __builtin_amdgcn_raw_buffer_store_b128(*(const U4 *)&sQ[w][qw + i * RI + lrow][lcol * VL], rPsi,
+                                                       (unsigned)(poff + (i * RI - 3 * CH) * pstep), 0, kPsiAux);
+        };
+        auto commit = [&](int q0) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) *(U4 *)&sQ[w][q0 + i * RI + lrow][lcol * VL] = pq[i];
+            if constexpr (SM) {  // as byte offsets into the sigma table
+                constexpr unsigned kSh = sizeof(T) == 4 ? 2 : 3;
+                *(U32x2 *)&sMt[w][q0 + mat_row(sx, lane)][8 * (lane & 7)] =
+                    U32x2{(pmt[0] & 0x1F1F1F1Fu) << kSh, (pmt[1] & 0x1F1F1F1Fu) << kSh};
+            }
+            bool okY = offy == kNone || Face::ok(pfy, stamp);
+            bool okZ = offz == kNone || Face::ok(pfz, stamp);
+            int spins = 0;
+            while (good && __any(!(okY && okZ))) {
+                __builtin_amdgcn_s_sleep(1);
+                if (!okY) {
+                    Face::template load<kVolatileSC1>(pfy, rFY, offy);
+                    okY = Face::ok(pfy, stamp);
+                }
+                if (!okZ) {
+                    Face::template load<kVolatileSC1>(pfz, rFZ, offz);
+                    okZ = Face::ok(pfz, stamp);
+                }
+                good = !gave_up(++spins, a0.sweep_spin_limit);
+            }
+            sF[w][0][e][ro] = Face::value(pfy);
+            sF[w][1][e][ro] = Face::value(pfz);
+        };
+        T px = T(0), oy = T(0), oz = T(0);
+        int s0 = skew ? RQ - skew : 0;  // ring slot of the lane's row at the next chunk's step 0
+
+        // rows -14 .. -1 (and two slots more): zero source, zero sigma
+#pragma unroll
+        for (int i = 0; i < 16 * RB / 1024; ++i) ((U4 *)&sQ[w][RQ - 16][0])[i * 64 + lane] = U4{0, 0, 0, 0};
+        if constexpr (SM) {
+            constexpr unsigned kZ = (kSigTab - 1) * sizeof(T) * 0x01010101u;
+            ((U4 *)&sMt[w][RQ - 16][0])[lane] = U4{kZ, kZ, kZ, kZ};
+        }
+        load_rows(-ph);
+        __builtin_amdgcn_sched_barrier(0);
+        {
+            int so = sig_off(-skew);
             if constexpr (!SM) {
-                int so = sig_off(-skew);
 #pragma unroll
                 for (int b = 0; b < CH; ++b, so += sstep) ps[b] = Sig::load(rSig, (unsigned)so);
             }
-            __builtin_amdgcn_sched_barrier(0);
-            for (int c = 0; c < nchunks; ++c) {
-                if (!commit(c)) {
-                    good = false;
-                    break;
-                }
-                if (c == cnext && k == npen - 1 && role == R - 1 && slot == 0 && lane == 0)
-                    sNext = atomicAdd(&ctr[0], 1);
-                load_rows(c + 1);
-                steps(c);
-                if (!writeback(c)) {
-                    good = false;
-                    break;
-                }
+            if constexpr (MODE == kTrans) {
+                int mo = mbase - (skew + ph) * mstep + pl;
+#pragma unroll
+                for (int b = 0; b < CH; ++b, mo += mstep) pm[b] = __builtin_amdgcn_raw_buffer_load_b8(rMask, mo, 0, 0);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+        // all out of range: only mirrors the loop's issue order, so that the
+        // wait at the loop's head can leave the newest stores in flight
+        put_rows(0);
+        put_faces(-64);
+        __builtin_amdgcn_sched_barrier(0);
+        int q0 = 0;  // ring slot of the chunk's first new row
+        // chunks c in [link_lo, link_hi) count on this lane's link
+        const int link_lo = lane == 2 || lane == 3 ? 0 : first_out;
+        const int link_hi = lane == 1 ? (outZ ? nchunks : 0) : lane == 2 ? (inY ? nlink : 0)
+                            : lane == 3 ? (inZ ? nlink : 0) : (outY ? nchunks : 0);
+        // one way out, at the end of the body (a chunk whose wait gave up runs
+        // on over garbage; the launch is reported as failed): with another the
+        // compiler would wait at the loop's head for the newest stores
+        for (int c = 0; good && c < nchunks; ++c) {
+            commit(q0);
+            // this chunk's own inputs from the rings
+            int sq[CH];
+            T q[CH], sg[CH];
+#pragma unroll
+            for (int b = 0; b < CH; ++b) {
+                sq[b] = s0 + b < RQ ? s0 + b : s0 + b - RQ;
+                q[b] = sQ[w][sq[b]][pl];
+                if constexpr (SM) sg[b] = *(const T *)((const char *)sSigT + sMt[w][sq[b]][pl]);
+            }
+            if (c == cnext && tw == 0 && !once) {
+                if (lane == 0) tnext = atomicAdd(&ctr[opaque0], 1);
+                have_next = true;
+            }
+            const int uo = uin - 7;
+            poff += CH * pstep;
+            uin += CH;
+            load_rows(CH * (c + 1) - ph);
+            // inflow chunks there, outflow slots free
+            const int step_ = c >= link_lo && c < link_hi ? 1 : 0;
+            const int want = done + (lane == 2 || lane == 3 ? step_ : 1 - NS);
+            int spins = 0;
+            while (good && __any(lds_get(watch) < want)) {
+                __builtin_amdgcn_s_sleep(1);
+                good = !gave_up(++spins, lds_limit);
+            }
+            T fy[CH], fz[CH], po[CH], yo_[CH], zo_[CH];
+            {
+                const T *const fyr = inY ? sF[wy][2 + scy][kp] : sF[w][0][kp];
+                const T *const fzr = inZ ? sF[wz][2 + NS + scz][jp] : sF[w][1][jp];
+#pragma unroll
+                for (int i = 0; i < CH / VL; ++i) {
+                    *(U4 *)&fy[i * VL] = *(const U4 *)&fyr[i * VL];
+                    *(U4 *)&fz[i * VL] = *(const U4 *)&fzr[i * VL];
+                }
+            }
+            const int ir0 = CH * c - skew;  // row + ph at step 0 of the chunk
+            int so = sig_off(ir0 + CH);
+            int mo = mbase + (ir0 - ph) * mstep + pl;
+            T inz = lane_from(oz, srcZ);
+#pragma unroll
+            for (int b = 0; b < CH; ++b, so += sstep, mo += mstep) {
+                T iny = lane_shr1(oy);
+                iny = yb ? fy[b] : iny;
+                inz = zb ? fz[b] : inz;
+                T ox_, oy_, oz_, inz_next;
+                unsigned mk = 0;
+                if constexpr (MODE == kTrans) mk = pm[b];
+                if constexpr (!SM) sg[b] = Sig::value(ps[b], sSigT);
+                po[b] = dd_update<T, MODE>(q[b], sg[b], cx, cy, cz, csum, px, iny, inz, ox_, oy_, oz_, mk,
+                                           [&](T z) { inz_next = lane_from(z, srcZ); });
+                if constexpr (MODE == kRecord)
+                    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)mk, rMask, mo, 0, 0);
+                if constexpr (MODE == kTrans)
+                    pm[b] = __builtin_amdgcn_raw_buffer_load_b8(rMask, mo + CH * mstep, 0, 0);
+                yo_[b] = oy_;
+                zo_[b] = oz_;
+                px = ox_;
+                oy = oy_;
+                oz = oz_;
+                inz = inz_next;
+                if constexpr (!SM) ps[b] = Sig::load(rSig, (unsigned)so);
+            }
+            if (yo) {
+#pragma unroll
+                for (int i = 0; i < CH / VL; ++i) *(U4 *)&sF[w][2 + spy][kp][i * VL] = *(U4 *)&yo_[i * VL];
+            }
+            if (zo) {
+#pragma unroll
+                for (int i = 0; i < CH / VL; ++i) *(U4 *)&sF[w][2 + NS + spz][jp][i * VL] = *(U4 *)&zo_[i * VL];
+            }
+            // hand the outflow over and free the inflow before anything else
+            done += step_;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            if (tells) __hip_atomic_store(tell, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+            for (int b = 0; b < CH; ++b) sQ[w][sq[b]][pl] = po[b];
+            // psi rows 8c-16 .. 8c-9 (counted with the idle steps) are
+            // complete, and go back
+            const int qw = q0 == RQ - CH ? 0 : q0 + CH;
+            put_rows(qw);
+            put_faces(uo);
+            const bool takes = c < nlink, gives = c >= first_out;
+            if (inY && takes) scy = scy + 1 < NS ? scy + 1 : 0;
+            if (inZ && takes) scz = scz + 1 < NS ? scz + 1 : 0;
+            if (outY && gives) spy = spy + 1 < NS ? spy + 1 : 0;
+            if (outZ && gives) spz = spz + 1 < NS ? spz + 1 : 0;
+            q0 = qw;
+            s0 = s0 + CH < RQ ? s0 + CH : s0 + CH - RQ;
+        }
     }
+    if (!good) abort_all();
 }
 
 // Before every sweep: ticket counter back to zero and the next epoch for the
@@ -1205,50 +1379,78 @@ static const void *sweep_kernel_xcd(int wpb, int mode, bool sm, bool nt)
 
 bool sweep_xcd_supported(bool fp64, int mode, int wpb) { return !fp64 && mode == kFixup && wpb >= 1 && wpb <= 4; }
 
-// Column-relay variants (forward cell modes): (directions, roles) per block
-// of W x R waves.
-#define DSN_COL_F32(X) X(1, 2) X(1, 4) X(2, 2) X(2, 4)
-#define DSN_COL_F64(X) X(1, 2) X(1, 4)
+// Tile variants: (teams, r) as the launch shape names them, and the waves of a
+// team.  A block holds w teams of 4 waves (r = 2), or for r = 4 one of 16 or
+// two of 8 in FP32 and one of 8 in FP64, whose rows take twice the LDS.
+#define DSN_TILE_F32(X) X(1, 2) X(1, 4) X(2, 2) X(2, 4)
+#define DSN_TILE_F64(X) X(1, 2) X(1, 4)
+static int tile_team(bool fp64, int w, int r) { return r == 2 ? 4 : !fp64 && w == 1 ? 16 : 8; }
 
-int sweep_col_choices(bool fp64, int *w_out, int *r_out)
+int sweep_tile_choices(bool fp64, int *w_out, int *r_out)
 {
     int n = 0;
 #define DSN_PUT2(W, R) w_out[n] = W, r_out[n++] = R;
     if (fp64) {
-        DSN_COL_F64(DSN_PUT2)
+        DSN_TILE_F64(DSN_PUT2)
     } else {
-        DSN_COL_F32(DSN_PUT2)
+        DSN_TILE_F32(DSN_PUT2)
     }
 #undef DSN_PUT2
     return n;
 }
 
-template <typename T, int MODE, int W, int R>
-static const void *sweep_kernel_col_nt(bool sm, bool nt)
+// The tile of a team on an NJ x NK grid of pencils: of the factorings of its
+// wave count the one with the fewest tiles, then the fewest tile diagonals
+// (hops through memory), then the squarest.
+void sweep_tile(bool fp64, int w, int r, int NJ, int NK, int *ty, int *tz)
 {
-    if (nt)
-        return sm ? (const void *)&k_sweep_col<T, MODE, W, R, true, true>
-                  : (const void *)&k_sweep_col<T, MODE, W, R, false, true>;
-    return sm ? (const void *)&k_sweep_col<T, MODE, W, R, true, false>
-              : (const void *)&k_sweep_col<T, MODE, W, R, false, false>;
+    const int n = tile_team(fp64, w, r);
+    long best = -1;
+    for (int y = 1; y <= n; ++y) {
+        if (n % y) continue;
+        const int z = n / y, nj = (NJ + y - 1) / y, nk = (NK + z - 1) / z;
+        const long cost = ((long)nj * nk * 4096 + nj + nk) * 64 + (y > z ? y - z : z - y);
+        if (best < 0 || cost < best) best = cost, *ty = y, *tz = z;
+    }
 }
+
+template <typename T, int MODE, int NW>
+static const void *sweep_kernel_tile_of(bool sm, bool nt)
+{
+    if constexpr (MODE == kDD || MODE == kFixup) {
+        if (nt)
+            return sm ? (const void *)&k_sweep_tile<T, MODE, NW, true, true>
+                      : (const void *)&k_sweep_tile<T, MODE, NW, false, true>;
+    }
+    return sm ? (const void *)&k_sweep_tile<T, MODE, NW, true, false>
+              : (const void *)&k_sweep_tile<T, MODE, NW, false, false>;
+}
+
+template <typename T, int NW>
+static const void *sweep_kernel_tile_nw(int mode, bool sm, bool nt)
+{
+    switch (mode) {
+    case kDD: return sweep_kernel_tile_of<T, kDD, NW>(sm, nt);
+    case kFixup: return sweep_kernel_tile_of<T, kFixup, NW>(sm, nt);
+    case kRecord: return sweep_kernel_tile_of<T, kRecord, NW>(sm, nt);
+    case kTrans: return sweep_kernel_tile_of<T, kTrans, NW>(sm, nt);
+    default: return nullptr;
+    }
+}
+
+// waves of a block of the tile shape (w, r)
+static int tile_waves(bool fp64, int w, int r) { return w * tile_team(fp64, w, r); }
 
 template <typename T>
-static const void *sweep_kernel_col(int w, int r, int mode, bool sm, bool nt)
+static const void *sweep_kernel_tile(int w, int r, int mode, bool sm, bool nt)
 {
-    if (mode != kDD && mode != kFixup) return nullptr;
-#define DSN_CPICK(W, R)                                                                                  if (w == W && r == R)                                                                                   return mode == kDD ? sweep_kernel_col_nt<T, kDD, W, R>(sm, nt) : sweep_kernel_col_nt<T, kFixup, W, R>(sm, nt);
-    if constexpr (sizeof(T) == 8) {
-        DSN_COL_F64(DSN_CPICK)
-    } else {
-        DSN_COL_F32(DSN_CPICK)
-    }
-#undef DSN_CPICK
+    const int nw = tile_waves(sizeof(T) == 8, w, r);
+    if (nw == 4) return sweep_kernel_tile_nw<T, 4>(mode, sm, nt);
+    if (nw == 8) return sweep_kernel_tile_nw<T, 8>(mode, sm, nt);
+    if constexpr (sizeof(T) == 4)
+        if (nw == 16) return sweep_kernel_tile_nw<T, 16>(mode, sm, nt);
     return nullptr;
 }
-
-// Dynamic LDS of a column-relay block: one pencil of y-face rows per wave.
-static size_t col_lds_bytes(int w, int r, int nx, size_t tsize) { return (size_t)w * r * nx * 8 * tsize; }
 
 bool sweep_tagged_faces(bool fp64, int mode, int wpb, int xcd)
 {
@@ -1363,19 +1565,21 @@ int launch_sweep_multi(const SolveArgs<T> &a, const SolveArgs<T> *host_tab, int 
     return 1;
 }
 
-// Resident blocks of the column-relay sweep with w directions and r roles per
-// block for an x extent of nx (grid size), 0 if there is no such kernel or
-// its LDS does not fit.
+// Resident blocks of the tile sweep of shape (w, r) in cell mode `mode` (grid
+// size), 0 if there is no such kernel, or for an x extent beyond the shapes'
+// range: w * r pencils of an x extent must fit a CU's LDS (nx up to 970 for
+// (1, 4) in FP32, 357 in FP64), the range pinned shapes have been accepted for.
 template <typename T>
-int sweep_grid_col(int w, int r, int mode, int nx, int n_cu)
+int sweep_grid_tile(int w, int r, int mode, int nx, int n_cu)
 {
+    const long ts = sizeof(T);
+    if (w * r * (24 * 64 * ts + 4 * 16 * 8 * ts + 24 * 64 + nx * 8L * ts) + 256 > 160 * 1024) return 0;
     int per_cu = 1 << 30;
     for (int sm = 0; sm < 2; ++sm) {
-        const void *f = sweep_kernel_col<T>(w, r, mode, sm != 0, false);
+        const void *f = sweep_kernel_tile<T>(w, r, mode, sm != 0, false);
         if (!f) return 0;
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * w * r, col_lds_bytes(w, r, nx, sizeof(T))) !=
-                hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * tile_waves(ts == 8, w, r), 0) != hipSuccess ||
             n < 1) {
             (void)hipGetLastError();
             return 0;
@@ -1407,12 +1611,12 @@ int sweep_grid(int wpb, int mode, int n_cu)
 template <typename T>
 int launch_sweeps(const SolveArgs<T> &a, int g, hipStream_t s, hipEvent_t ev_before, hipEvent_t ev_after)
 {
-    // per-XCD queues where such a kernel is built (FP32 fixup sweeps), else
-    // the global queue
-    const bool col = sweep_uses_col(a);
-    const bool xcd = !col && a.sweep_xcd > 0 && sweep_xcd_supported(sizeof(T) == 8, a.sweep_mode, a.sweep_wpb);
+    // tile items, per-XCD queues where such a kernel is built (FP32 fixup
+    // sweeps), else pencil items on the global queue
+    const bool tile = a.sweep_relay > 0;
+    const bool xcd = !tile && a.sweep_xcd > 0 && sweep_xcd_supported(sizeof(T) == 8, a.sweep_mode, a.sweep_wpb);
     const bool nt = a.stream_nt != 0;
-    const void *f = col ? sweep_kernel_col<T>(a.sweep_wpb, a.sweep_relay, a.sweep_mode, a.sig_from_mat != 0, nt)
+    const void *f = tile ? sweep_kernel_tile<T>(a.sweep_wpb, a.sweep_relay, a.sweep_mode, a.sig_from_mat != 0, nt)
                     : xcd ? sweep_kernel_xcd<T>(a.sweep_wpb, a.sweep_mode, a.sig_from_mat != 0, nt)
                           : sweep_kernel_of<T>(a.sweep_wpb, a.sweep_mode, a.sig_from_mat != 0, nt);
     if (!f) return 0;
@@ -1422,18 +1626,14 @@ int launch_sweeps(const SolveArgs<T> &a, int g, hipStream_t s, hipEvent_t ev_bef
         grid = (grid + a.sweep_xcd - 1) / a.sweep_xcd * a.sweep_xcd;
     SolveArgs<T> arg = a;
     if (!xcd) arg.sweep_xcd = 0;
-    if (a.sweep_relay > 0 && !col) {
-        // a handle tuned to column-relay items sweeps the other cell modes
-        // (the adjoint's) with pencil items of as many directions per block
-        arg.sweep_relay = 0;
-        arg.sweep_nitems = a.sweep_nitems * a.g.NJ;
-        grid = (unsigned)(arg.sweep_grid < arg.sweep_nitems ? arg.sweep_grid : arg.sweep_nitems);
+    int waves = a.sweep_wpb;
+    if (tile) {
+        sweep_tile(sizeof(T) == 8, a.sweep_wpb, a.sweep_relay, a.g.NJ, a.g.NK, &arg.tile_y, &arg.tile_z);
+        waves = tile_waves(sizeof(T) == 8, a.sweep_wpb, a.sweep_relay);
     }
     void *params[2] = {&arg, &g};
-    const int waves = col ? a.sweep_wpb * a.sweep_relay : a.sweep_wpb;
-    const size_t lds = col ? col_lds_bytes(a.sweep_wpb, a.sweep_relay, a.g.nx, sizeof(T)) : 0;
     if (ev_before) (void)hipEventRecord(ev_before, s);
-    (void)hipLaunchKernel(f, dim3(grid), dim3(64 * waves), params, lds, s);
+    (void)hipLaunchKernel(f, dim3(grid), dim3(64 * waves), params, 0, s);
     if (ev_after) (void)hipEventRecord(ev_after, s);
     if (xcd)
         hipLaunchKernelGGL(k_xcd_drained, dim3(1), dim3(64), 0, s, a.ctl, a.G, g, a.S, a.sweep_ctr, a.sweep_xcd,
@@ -1455,8 +1655,8 @@ void launch_checksum(const void *x, long n_words, unsigned long long *out, hipSt
 
 template int sweep_grid<float>(int, int, int);
 template int sweep_grid<double>(int, int, int);
-template int sweep_grid_col<float>(int, int, int, int, int);
-template int sweep_grid_col<double>(int, int, int, int, int);
+template int sweep_grid_tile<float>(int, int, int, int, int);
+template int sweep_grid_tile<double>(int, int, int, int, int);
 template int launch_sweeps<float>(const SolveArgs<float> &, int, hipStream_t, hipEvent_t, hipEvent_t);
 template int launch_sweeps<double>(const SolveArgs<double> &, int, hipStream_t, hipEvent_t, hipEvent_t);
 template int sweep_grid_multi<float>(int, int, int);

@@ -236,7 +236,7 @@ class Problem:
         """Solves every source; returns dict(phi_total [n_src][G][V] cuda
         FP64 tensor, phi_u (or None), iters [n_src][G], residual, updates,
         seconds, status, stages, sweep_bytes, sweep_shape = (waves per
-        block, blocks, per-XCD queues, column-relay roles)).  autotune: time the sweep launch
+        block, blocks, per-XCD queues, R of a tile shape or 0)).  autotune: time the sweep launch
         shapes at this call if the handle has not been tuned (see
         sweep_tuning(), set_sweep_shape()).
         combine: the sources act together in one solve (a CT ring); the
@@ -319,7 +319,7 @@ class Problem:
 
     def sweep_tuning(self):
         """The launch shapes the autotune timed: list of (waves per block,
-        blocks, per-XCD queues, column-relay roles, ms per sweep; negative
+        blocks, per-XCD queues, R of a tile shape or 0, ms per sweep; negative
         ms: the shape's result differed from the default shape's and it was
         not used), empty before any autotune."""
         cap = 64
@@ -343,7 +343,7 @@ class Problem:
     def set_sweep_shape(self, waves_per_block, blocks, xcd_queues=0, relay=0):
         """Pins the sweep launch shape (e.g. one from another handle's
         sweep_tuning()); the handle then counts as tuned.  relay > 0: the
-        column-relay sweep with that many roles (dsn_set_sweep_shape)."""
+        tile sweep of the shape (waves_per_block, relay) (dsn_set_sweep_shape)."""
         _check(lib().dsn_set_sweep_shape(self.handle, int(waves_per_block), int(blocks), int(xcd_queues),
                                          int(relay)))
 
