@@ -180,10 +180,9 @@ typedef struct {
                                    group in lockstep on opts->stream, and each
                                    source iteration is ONE sweep launch over
                                    every (problem, source) pair, then one
-                                   moments launch and one convergence-test
-                                   launch over all of them, replayed as one
-                                   HIP graph; autotune = 1 times that
-                                   launch's shapes at the first group.  Needs
+                                   moments launch over all of them; autotune =
+                                   1 times the sweep launch's shapes at the
+                                   first group.  Needs
                                    the same fixup setting in every problem and
                                    all with or all without a per-voxel density
                                    (else DSN_ERR_UNSUPPORTED).

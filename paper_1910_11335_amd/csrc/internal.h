@@ -62,6 +62,21 @@ __host__ __device__ inline long psi_index(const Geom &g, int Nd, long v)
     return v + (v / PL) * (long)(Nd - 1) * PL;
 }
 
+// Sweep counter block: [0] next ticket, [1] abort flag, [2] epoch of the next
+// sweep's tagged face words, [kQueueCtr + q] next ticket of XCD q's queue.  It
+// is made ready for the next sweep after every sweep, before anything else
+// sweeps with it: tickets back to zero and the next epoch, kept in
+// [1, 2^31 - 1] (invalidated words hold all ones).  Called by one block.
+constexpr int kQueueCtr = 4;
+__device__ inline void sweep_counters_next(int *ctr, int thread)
+{
+    if (thread < 8) ctr[kQueueCtr + thread] = 0;
+    if (thread == 0) {
+        ctr[0] = 0;
+        ctr[2] = (int)((unsigned)ctr[2] % 0x7FFFFFFEu + 1u);
+    }
+}
+
 constexpr int kSrcPar = 12;  // doubles of source parameters per source
 
 // Per-solve argument block for the kernels (all device pointers).
@@ -87,10 +102,12 @@ struct SolveArgs {
     T *sig;                   // [Vp] rho * sigma_t of the current group
     T *psi;                   // [NJ*NK][Nd][nx*64] Q, then psi, in place (pencil-major: psi_index)
     unsigned long long *faceY, *faceZ;  // [Nd][NJ*NK][nx][8][words]: tagged face values
-    double *part;             // [n_blocks][4] residual partials: two sums (L2), two maxima (rule 1)
+    double *part;             // [n_blocks][4] residual partials: two sums (L2), two maxima (rule 1), written
+                              // and read around the L2 (blocks of one source run on several XCDs)
     Ctl *ctl;                 // [G]
     // persistent sweep work queue
-    int *sweep_ctr;           // [3]: next ticket, abort flag, epoch of the current sweep
+    int *sweep_ctr;           // the sweep counter block (sweep_counters_next)
+    int *blk_done;            // [S]: blocks of the running moments pass that have written their partials
     int *face_par;            // [S]: sign-bit parity of the next sweep's face words
     const int *sweep_dstart;  // [NJ+NK] first ticket of each pencil diagonal (+ total)
     int sweep_nitems;
@@ -144,6 +161,7 @@ __host__ __device__ inline SolveArgs<T> at_source(SolveArgs<T> a, int s)
         a.ctl += (long)s * a.G;
         a.src_par += (long)kSrcPar * s;
         a.face_par += s;
+        a.blk_done += s;
         a.src_spec += (long)s * a.G;
     }
     return a;
@@ -174,17 +192,20 @@ int sweep_tile_choices(bool fp64, int *w_out, int *r_out);  // (teams, r) of the
 void sweep_tile(bool fp64, int w, int r, int NJ, int NK, int *ty, int *tz);  // the tile of a team, in pencils
 template <typename T>
 int sweep_grid_tile(int w, int r, int mode, int nx, int n_cu);
+// follow: launch_d2m with the same arguments comes next on the stream;
 // ev_before / ev_after (may be null): recorded on s right around the sweep
-// kernel itself (after the ticket reset, before the parity flip)
+// kernel itself
 template <typename T>
-int launch_sweeps(const SolveArgs<T> &a, int g, hipStream_t s, hipEvent_t ev_before = nullptr,
+int launch_sweeps(const SolveArgs<T> &a, int g, hipStream_t s, bool follow, hipEvent_t ev_before = nullptr,
                   hipEvent_t ev_after = nullptr);
+template <typename T>
+bool sweep_flips_parity(const SolveArgs<T> &a);
 // fused batches: several problems in one sweep launch
 int sweep_multi_choices(bool fp64, int *out);
 template <typename T>
 int sweep_grid_multi(int wpb, int mode, int n_cu);
 template <typename T>
-int launch_sweep_multi(const SolveArgs<T> &a, const SolveArgs<T> *host_tab, int n, int g, hipStream_t s,
+int launch_sweep_multi(const SolveArgs<T> &a, const SolveArgs<T> *host_tab, int n, int g, hipStream_t s, bool follow,
                        hipEvent_t ev_before = nullptr, hipEvent_t ev_after = nullptr);
 bool sweep_xcd_supported(bool fp64, int mode, int wpb);  // a per-XCD-queue sweep kernel is built
 bool sweep_tagged_faces(bool fp64, int mode, int wpb, int xcd);  // the launch uses tagged (not sign-parity) words
@@ -193,7 +214,7 @@ void launch_checksum(const void *x, long n_words, unsigned long long *out, hipSt
 template <typename T>
 int launch_d2m(const SolveArgs<T> &a, int g, bool expand, hipStream_t s);
 template <typename T>  // every (problem, source) pair of a fused batch
-int launch_d2m_multi(const SolveArgs<T> *tab, const SolveArgs<T> &a, int n, long vp_max, int s_max, bool nt, int g,
+int launch_d2m_multi(const SolveArgs<T> *tab, const SolveArgs<T> &a, int n, long vp_max, int s_max, int g,
                      hipStream_t s);
 template <typename T>
 void launch_finalize(const SolveArgs<T> &a, int g, double *phi_total, double *phi_unc, hipStream_t s);

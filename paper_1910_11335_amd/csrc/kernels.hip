@@ -7,8 +7,8 @@
 //   k_sweep  diamond-difference transport sweep of every direction (sweep.hip)
 //            (section II.B: voxels with i+j+k = S are independent)
 //   k_d2m    moments phi_lm = sum_n w_n R_lm(Omega_n) psi_n (eq. 3 for lm = 00)
-//            accumulated in FP64, plus the residual partial sums
-//   k_resid  relative change of phi_00 in FP64, convergence flag
+//            accumulated in FP64, then, by the last block of a source, the
+//            relative change of phi_00 in FP64 and the convergence flag
 // and before the iterations k_group_source builds F (first-collision source
 // of eq. 5 from the ray-traced uncollided fluence, plus downscatter from the
 // converged higher groups).
@@ -571,91 +571,13 @@ __device__ __forceinline__ double wave_max(double x)
     return x;
 }
 
-// EXPAND: also form the next iteration's directional source from the new
-// moments (the work of k_m2d, while the moments are still in registers), so
-// an iteration is one sweep and one pass over psi.
-// Residual partials of each block: the sums of (phi00_new - phi00_old)^2 and
-// phi00_new^2, and for the pointwise rule the largest |total| = |phi_u +
-// phi00_new| and the largest |phi00_new - phi00_old| / |total| over voxels
-// whose |total| reaches 1e-6 of the previous iterate's largest.  Maxima do not
-// depend on the order of reduction.
-template <typename T, int L, bool EXPAND, bool NT>
-__device__ __forceinline__ void d2m_body(const SolveArgs<T> &a, int g, unsigned bx)
+__device__ __forceinline__ double around_l2_load(const double *p)
 {
-    constexpr int Nm = (L + 1) * (L + 1);
-    const Ctl &cg = a.ctl[g];
-    if (cg.done) return;
-    const int rule = cg.rule;
-    const double floor_t = 1e-6 * cg.tmax;
-    const long v = bx * 256L + threadIdx.x;
-    const long Vp = a.g.Vp;
-    const int D = a.D;
-    double d2 = 0.0, n2 = 0.0, tm = 0.0, dm = 0.0;
-    constexpr LmTables tab = make_lm_tables();
-    __shared__ T stage[2][8][256];
-    const bool coop = sizeof(T) == 8 && block_in_pencil(a.g, bx);
-    if (v < Vp) {
-        double acc[Nm];
-#pragma unroll
-        for (int lm = 0; lm < Nm; ++lm) acc[lm] = 0.0;
-        const T *in = a.psi + psi_index(a.g, a.Nd, v);
-        const long PL = (long)a.g.nx * 64;  // direction stride of pencil-major psi
-        const double *D0 = a.D0;
-        for (int p = 0; p < D; ++p) {
-            double x[8];
-#pragma unroll
-            for (int o = 0; o < 8; ++o) x[o] = (double)ld_stream<NT>(&in[(long)(o * D + p) * PL]);
-            fwht8(x);
-#pragma unroll
-            for (int lm = 0; lm < Nm; ++lm) acc[lm] += D0[p * Nm + lm] * x[tab.cls[lm]];
-        }
-        double *ph = a.phic + (long)g * Nm * Vp + v;
-        const double old = ld_stream<NT>(&ph[0]);
-#pragma unroll
-        for (int lm = 0; lm < Nm; ++lm) st_stream<NT>(acc[lm], &ph[(long)lm * Vp]);
-        const double dd = acc[0] - old;
-        d2 = dd * dd;
-        n2 = acc[0] * acc[0];
-        if (rule == 1) {
-            const double t = fabs(a.phiu[(long)g * Vp + v] + acc[0]);
-            tm = t;
-            if (t > 0.0 && t >= floor_t) dm = fabs(dd) / t;
-        }
-        if (EXPAND) expand_source<T, L, NT>(a, g, v, [&](int lm) { return acc[lm]; }, coop, stage);
-    }
-    __shared__ double red[4][4];
-    d2 = wave_sum(d2);
-    n2 = wave_sum(n2);
-    tm = wave_max(tm);
-    dm = wave_max(dm);
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) { red[0][w] = d2; red[1][w] = n2; red[2][w] = tm; red[3][w] = dm; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double *pb = a.part + 4 * bx;
-        pb[0] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-        pb[1] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
-        pb[2] = fmax(fmax(red[2][0], red[2][1]), fmax(red[2][2], red[2][3]));
-        pb[3] = fmax(fmax(red[3][0], red[3][1]), fmax(red[3][2], red[3][3]));
-    }
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-
-template <typename T, int L, bool EXPAND, bool NT>
-__global__ __launch_bounds__(256) void k_d2m(SolveArgs<T> a0, int g)
+__device__ __forceinline__ void around_l2_store(double *p, double v)
 {
-    d2m_body<T, L, EXPAND, NT>(at_source(a0, blockIdx.y), g, blockIdx.x);
-}
-
-// The moments of every (problem, source) pair of a fused batch in one
-// launch: blockIdx.z = problem (its argument block in tab), blockIdx.y =
-// source, blockIdx.x = voxel block; blocks past a smaller problem's voxels
-// or sources leave at once.
-template <typename T, int L, bool EXPAND, bool NT>
-__global__ __launch_bounds__(256) void k_d2m_multi(const SolveArgs<T> *tab, int g)
-{
-    const SolveArgs<T> &a0 = tab[blockIdx.z];
-    if ((long)blockIdx.x * 256 >= a0.g.Vp || (int)blockIdx.y >= a0.S) return;
-    d2m_body<T, L, EXPAND, NT>(at_source(a0, blockIdx.y), g, blockIdx.x);
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Convergence test of one group (section II.C leaves the criterion open).
@@ -667,15 +589,20 @@ __global__ __launch_bounds__(256) void k_d2m_multi(const SolveArgs<T> *tab, int 
 // source iteration shrinks the change per step, so the changes still to come
 // sum to about d rho / (1 - rho).  The first iterate (no rho yet) never stops
 // rule 1 unless r = 0.
+//
+// Run by the block of the moments pass that finishes last, in a fixed order of
+// the partials.  As a kernel of its own it cost every iteration a launch, 4 to
+// 11 us, as did the two small kernels that readied the sweep counters and the
+// face parity, which the moments pass does too now: on a 32^3 mesh 14 us of the
+// 94 us of an iteration.
 __device__ __forceinline__ void resid_body(Ctl *ctl, int g, const double *part, int nblk)
 {
-    if (ctl[g].done) return;
     double s0 = 0.0, s1 = 0.0, tm = 0.0, dm = 0.0;
     for (int b = threadIdx.x; b < nblk; b += 256) {
-        s0 += part[4 * b];
-        s1 += part[4 * b + 1];
-        tm = fmax(tm, part[4 * b + 2]);
-        dm = fmax(dm, part[4 * b + 3]);
+        s0 += around_l2_load(&part[4 * b]);
+        s1 += around_l2_load(&part[4 * b + 1]);
+        tm = fmax(tm, around_l2_load(&part[4 * b + 2]));
+        dm = fmax(dm, around_l2_load(&part[4 * b + 3]));
     }
     __shared__ double red[4][4];
     s0 = wave_sum(s0);
@@ -729,20 +656,111 @@ __device__ __forceinline__ void resid_body(Ctl *ctl, int g, const double *part, 
     ctl[g] = c;
 }
 
-__global__ __launch_bounds__(256) void k_resid(Ctl *ctl0, int G, long str_part, int g, const double *part0,
-                                              int nblk)
+// EXPAND: also form the next iteration's directional source from the new
+// moments (the work of k_m2d, while the moments are still in registers), so
+// an iteration is one sweep and one pass over psi.
+// Residual partials of each block: the sums of (phi00_new - phi00_old)^2 and
+// phi00_new^2, and for the pointwise rule the largest |total| = |phi_u +
+// phi00_new| and the largest |phi00_new - phi00_old| / |total| over voxels
+// whose |total| reaches 1e-6 of the previous iterate's largest.  Maxima do not
+// depend on the order of reduction.
+// flip: the sweep before left sign-parity face words, so the parity of a source
+// that ran flips (its next sweep rejects these words).
+template <typename T, int L, bool EXPAND, bool NT>
+__device__ __forceinline__ void d2m_body(const SolveArgs<T> &a, int g, unsigned bx, int flip)
 {
-    resid_body(ctl0 + (long)blockIdx.x * G, g, part0 + blockIdx.x * str_part, nblk);
+    constexpr int Nm = (L + 1) * (L + 1);
+    const Ctl &cg = a.ctl[g];
+    if (cg.done) return;
+    const int rule = cg.rule;
+    const double floor_t = 1e-6 * cg.tmax;
+    const long v = bx * 256L + threadIdx.x;
+    const long Vp = a.g.Vp;
+    const int D = a.D;
+    double d2 = 0.0, n2 = 0.0, tm = 0.0, dm = 0.0;
+    constexpr LmTables tab = make_lm_tables();
+    __shared__ T stage[2][8][256];
+    const bool coop = sizeof(T) == 8 && block_in_pencil(a.g, bx);
+    if (v < Vp) {
+        double acc[Nm];
+#pragma unroll
+        for (int lm = 0; lm < Nm; ++lm) acc[lm] = 0.0;
+        const T *in = a.psi + psi_index(a.g, a.Nd, v);
+        const long PL = (long)a.g.nx * 64;  // direction stride of pencil-major psi
+        const double *D0 = a.D0;
+        for (int p = 0; p < D; ++p) {
+            double x[8];
+#pragma unroll
+            for (int o = 0; o < 8; ++o) x[o] = (double)ld_stream<NT>(&in[(long)(o * D + p) * PL]);
+            fwht8(x);
+#pragma unroll
+            for (int lm = 0; lm < Nm; ++lm) acc[lm] += D0[p * Nm + lm] * x[tab.cls[lm]];
+        }
+        double *ph = a.phic + (long)g * Nm * Vp + v;
+        const double old = ld_stream<NT>(&ph[0]);
+#pragma unroll
+        for (int lm = 0; lm < Nm; ++lm) st_stream<NT>(acc[lm], &ph[(long)lm * Vp]);
+        const double dd = acc[0] - old;
+        d2 = dd * dd;
+        n2 = acc[0] * acc[0];
+        if (rule == 1) {
+            const double t = fabs(a.phiu[(long)g * Vp + v] + acc[0]);
+            tm = t;
+            if (t > 0.0 && t >= floor_t) dm = fabs(dd) / t;
+        }
+        if (EXPAND) expand_source<T, L, NT>(a, g, v, [&](int lm) { return acc[lm]; }, coop, stage);
+    }
+    __shared__ double red[4][4];
+    d2 = wave_sum(d2);
+    n2 = wave_sum(n2);
+    tm = wave_max(tm);
+    dm = wave_max(dm);
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) { red[0][w] = d2; red[1][w] = n2; red[2][w] = tm; red[3][w] = dm; }
+    __syncthreads();
+    const int nblk = (int)((Vp + 255) / 256);
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        double *pb = a.part + 4 * bx;
+        around_l2_store(&pb[0], (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]));
+        around_l2_store(&pb[1], (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
+        around_l2_store(&pb[2], fmax(fmax(red[2][0], red[2][1]), fmax(red[2][2], red[2][3])));
+        around_l2_store(&pb[3], fmax(fmax(red[3][0], red[3][1]), fmax(red[3][2], red[3][3])));
+        // the partials have arrived before the count says so (no cache to
+        // write back: they went around it)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        last = atomicAdd(a.blk_done, 1) == nblk - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    // every block of this source is past its look at ctl
+    resid_body(a.ctl, g, a.part, nblk);
+    if (threadIdx.x == 0) {
+        *a.blk_done = 0;
+        if (flip) *a.face_par ^= 1;
+    }
 }
 
-// The convergence test of every (problem, source) pair of a fused batch:
-// blockIdx.y = problem, blockIdx.x = source.
-template <typename T>
-__global__ __launch_bounds__(256) void k_resid_multi(const SolveArgs<T> *tab, int g)
+// The first block also makes the sweep counters ready for the next sweep
+// (the sweep before this launch has ended).
+template <typename T, int L, bool EXPAND, bool NT>
+__global__ __launch_bounds__(256) void k_d2m(SolveArgs<T> a0, int g, int flip)
 {
-    const SolveArgs<T> &a = tab[blockIdx.y];
-    if ((int)blockIdx.x >= a.S) return;
-    resid_body(a.ctl + (long)blockIdx.x * a.G, g, a.part + blockIdx.x * a.str_part, (int)((a.g.Vp + 255) / 256));
+    if (blockIdx.x == 0 && blockIdx.y == 0) sweep_counters_next(a0.sweep_ctr, threadIdx.x);
+    d2m_body<T, L, EXPAND, NT>(at_source(a0, blockIdx.y), g, blockIdx.x, flip);
+}
+
+// The moments of every (problem, source) pair of a fused batch in one
+// launch: blockIdx.z = problem (its argument block in tab), blockIdx.y =
+// source, blockIdx.x = voxel block; blocks past a smaller problem's voxels
+// or sources leave at once.  ctr: the batch's sweep counters.
+template <typename T, int L, bool EXPAND, bool NT>
+__global__ __launch_bounds__(256) void k_d2m_multi(const SolveArgs<T> *tab, int g, int flip, int *ctr)
+{
+    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) sweep_counters_next(ctr, threadIdx.x);
+    const SolveArgs<T> &a0 = tab[blockIdx.z];
+    if ((long)blockIdx.x * 256 >= a0.g.Vp || (int)blockIdx.y >= a0.S) return;
+    d2m_body<T, L, EXPAND, NT>(at_source(a0, blockIdx.y), g, blockIdx.x, flip);
 }
 
 // ---------------------------------------------------------------------------
@@ -1079,38 +1097,40 @@ int launch_m2d(const SolveArgs<T> &a, int g, hipStream_t s)
     return 1;
 }
 
+// Moments, next directional source and convergence test after a sweep with
+// the same arguments (launch_sweeps with follow).
 template <typename T>
 int launch_d2m(const SolveArgs<T> &a, int g, bool expand, hipStream_t s)
 {
-    const unsigned nb = nblk(a.g.Vp);
+    const dim3 grid(nblk(a.g.Vp), a.S);
+    const int flip = sweep_flips_parity(a) ? 1 : 0;
     if (expand && a.stream_nt) {
-        DSN_DISPATCH_L(a.L, hipLaunchKernelGGL((k_d2m<T, LL, true, true>), dim3(nb, a.S), dim3(256), 0, s, a, g));
+        DSN_DISPATCH_L(a.L, hipLaunchKernelGGL((k_d2m<T, LL, true, true>), grid, dim3(256), 0, s, a, g, flip));
     } else if (expand) {
-        DSN_DISPATCH_L(a.L, hipLaunchKernelGGL((k_d2m<T, LL, true, false>), dim3(nb, a.S), dim3(256), 0, s, a, g));
+        DSN_DISPATCH_L(a.L, hipLaunchKernelGGL((k_d2m<T, LL, true, false>), grid, dim3(256), 0, s, a, g, flip));
     } else {
-        DSN_DISPATCH_L(a.L, hipLaunchKernelGGL((k_d2m<T, LL, false, false>), dim3(nb, a.S), dim3(256), 0, s, a, g));
+        DSN_DISPATCH_L(a.L, hipLaunchKernelGGL((k_d2m<T, LL, false, false>), grid, dim3(256), 0, s, a, g, flip));
     }
-    hipLaunchKernelGGL(k_resid, dim3(a.S), dim3(256), 0, s, a.ctl, a.G, a.str_part, g, (const double *)a.part, (int)nb);
-    return 2;
+    return 1;
 }
 
-// Moments, residual partials, next directional source and convergence test
-// of every (problem, source) pair of a fused batch: two launches.  tab: the
-// problems' argument blocks on the device; a: any one of them (host), for
-// the moment order; vp_max, s_max: the largest padded voxel count and
-// source count among them; nt: non-temporal streams.
+// The same for every (problem, source) pair of a fused batch.  tab: the
+// problems' argument blocks on the device; a: the batch's sweep arguments;
+// vp_max, s_max: the largest padded voxel count and source count among them.
 template <typename T>
-int launch_d2m_multi(const SolveArgs<T> *tab, const SolveArgs<T> &a, int n, long vp_max, int s_max, bool nt, int g,
+int launch_d2m_multi(const SolveArgs<T> *tab, const SolveArgs<T> &a, int n, long vp_max, int s_max, int g,
                      hipStream_t s)
 {
     const dim3 grid(nblk(vp_max), s_max, n);
-    if (nt) {
-        DSN_DISPATCH_L(a.L, hipLaunchKernelGGL((k_d2m_multi<T, LL, true, true>), grid, dim3(256), 0, s, tab, g));
+    const int flip = sweep_flips_parity(a) ? 1 : 0;
+    if (a.stream_nt) {
+        DSN_DISPATCH_L(a.L, hipLaunchKernelGGL((k_d2m_multi<T, LL, true, true>), grid, dim3(256), 0, s, tab, g, flip,
+                                               a.sweep_ctr));
     } else {
-        DSN_DISPATCH_L(a.L, hipLaunchKernelGGL((k_d2m_multi<T, LL, true, false>), grid, dim3(256), 0, s, tab, g));
+        DSN_DISPATCH_L(a.L, hipLaunchKernelGGL((k_d2m_multi<T, LL, true, false>), grid, dim3(256), 0, s, tab, g, flip,
+                                               a.sweep_ctr));
     }
-    hipLaunchKernelGGL(k_resid_multi<T>, dim3(s_max, n), dim3(256), 0, s, tab, g);
-    return 2;
+    return 1;
 }
 
 template <typename T>
@@ -1179,9 +1199,9 @@ template int launch_m2d<float>(const SolveArgs<float> &, int, hipStream_t);
 template int launch_m2d<double>(const SolveArgs<double> &, int, hipStream_t);
 template int launch_d2m<float>(const SolveArgs<float> &, int, bool, hipStream_t);
 template int launch_d2m<double>(const SolveArgs<double> &, int, bool, hipStream_t);
-template int launch_d2m_multi<float>(const SolveArgs<float> *, const SolveArgs<float> &, int, long, int, bool, int,
+template int launch_d2m_multi<float>(const SolveArgs<float> *, const SolveArgs<float> &, int, long, int, int,
                                      hipStream_t);
-template int launch_d2m_multi<double>(const SolveArgs<double> *, const SolveArgs<double> &, int, long, int, bool, int,
+template int launch_d2m_multi<double>(const SolveArgs<double> *, const SolveArgs<double> &, int, long, int, int,
                                       hipStream_t);
 template void launch_finalize<float>(const SolveArgs<float> &, int, double *, double *, hipStream_t);
 template void launch_finalize<double>(const SolveArgs<double> &, int, double *, double *, hipStream_t);

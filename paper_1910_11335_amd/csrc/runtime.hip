@@ -6,7 +6,6 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
-#include <shared_mutex>
 #include <string>
 #include <thread>
 #include <vector>
@@ -170,23 +169,14 @@ struct SweepShape {
 constexpr int kMaxWpb = 16;     // waves per block: largest value built is below this
 constexpr int kMaxShapes = 64;  // (waves-per-block choices + per-XCD-queue + tile variants) x grid {1, 3/4, 1/2}
 constexpr int kMaxTile = 8;     // tile shapes (teams, r)
-constexpr int kCtrInts = 16;    // sweep counter block: ticket, abort flag, epoch, per-XCD tickets
+constexpr int kCtrInts = 16;    // sweep counter block (sweep_counters_next), one int spare
 // Polls of an upstream face word before a sweep gives up (about 1-2 us each
 // under load, so several seconds): far above any wait of a sweep that
 // progresses, also with other problems' sweeps on the GPU at the same time.
 constexpr int kDefaultWaitLimit = 1 << 22;
 
-// One captured source iteration (sweep + moments/next source + residual) of
-// one group, keyed by everything its kernels were launched with.
-struct IterGraph {
-    std::vector<unsigned char> key;
-    hipGraphExec_t exec = nullptr;
-};
-
 struct DeviceState {
     bool ready = false;
-    std::vector<IterGraph> graphs;  // most recently used last
-    hipStream_t capture = nullptr;  // private stream graphs are captured on
     hipStream_t batch_stream = nullptr;  // this problem's stream inside dsn_solve_batch
     int device = -1;
     std::vector<void *> allocs;
@@ -222,7 +212,7 @@ struct DeviceState {
     // per-source buffers are sized for S_cap sources of a batch
     int S_cap = 0, dstart_S = 0, dstart_wpb = 0, dstart_relay = 0;
     double *src_par = nullptr;
-    int *face_par = nullptr;
+    int *face_par = nullptr, *blk_done = nullptr;
     int S_cap_alloc = 0;  // sources the per-source buffers were sized for
     int wait_limit = 0;   // from the current call's options
     std::vector<void *> src_allocs;
@@ -397,29 +387,8 @@ Sizes sizes_of(const dsn_problem *p)
     return s;
 }
 
-// Device-wide calls (hipDeviceSynchronize, allocation and release) must not
-// run while a stream is being captured into a graph, and the problems of a
-// batch are driven from several host threads.  Captures hold this gate
-// shared; device-wide sections hold it exclusively (re-entrant per thread).
-std::shared_mutex g_capture_gate;
-thread_local int t_gate_depth = 0;
-
-struct DeviceWide {
-    DeviceWide()
-    {
-        if (t_gate_depth++ == 0) g_capture_gate.lock();
-    }
-    ~DeviceWide()
-    {
-        if (--t_gate_depth == 0) g_capture_gate.unlock();
-    }
-    DeviceWide(const DeviceWide &) = delete;
-    DeviceWide &operator=(const DeviceWide &) = delete;
-};
-
 dsn_status dev_alloc(DeviceState &d, void **ptr, size_t bytes)
 {
-    DeviceWide gate;
     void *q = nullptr;
     hipError_t e = hipMalloc(&q, bytes ? bytes : 16);
     if (e != hipSuccess)
@@ -433,7 +402,6 @@ dsn_status dev_alloc(DeviceState &d, void **ptr, size_t bytes)
 
 void dev_release(DeviceState &d)
 {
-    DeviceWide gate;
     if (d.device >= 0) (void)hipSetDevice(d.device);
     for (void *q : d.allocs) (void)hipFree(q);
     d.allocs.clear();
@@ -442,9 +410,6 @@ void dev_release(DeviceState &d)
     for (void *q : d.c_allocs) (void)hipFree(q);
     d.c_allocs.clear();
     if (d.h_ctl) (void)hipHostFree(d.h_ctl);
-    for (IterGraph &x : d.graphs)
-        if (x.exec) (void)hipGraphExecDestroy(x.exec);
-    if (d.capture) (void)hipStreamDestroy(d.capture);
     if (d.batch_stream) (void)hipStreamDestroy(d.batch_stream);
     d.timer.release();
     d = DeviceState();
@@ -474,7 +439,6 @@ int batch_limit(const dsn_problem *p)
 // leave words of the current parity behind.
 dsn_status invalidate_faces(DeviceState &d, size_t bytes)
 {
-    DeviceWide gate;
     DSN_HIP(hipDeviceSynchronize());
     DSN_HIP(hipMemset(d.faceY, 0xFF, bytes));
     DSN_HIP(hipMemset(d.faceZ, 0xFF, bytes));
@@ -488,7 +452,6 @@ dsn_status invalidate_faces(DeviceState &d, size_t bytes)
 // problem stays usable for the next call.
 dsn_status recover_from_abort(dsn_problem *p)
 {
-    DeviceWide gate;
     DeviceState &d = p->dev;
     const int zero2[2] = {0, 0};
     DSN_HIP(hipDeviceSynchronize());
@@ -516,7 +479,6 @@ dsn_status sweep_failed(dsn_problem *p, int flag)
 
 dsn_status ensure_batch(dsn_problem *p, int S)
 {
-    DeviceWide gate;
     DeviceState &d = p->dev;
     if ((double)S * sweep_items(p, 1) >= (double)(1 << 29))
         return fail(DSN_ERR_UNSUPPORTED, "too many sweep items (sources x directions x pencils) in one batch");
@@ -551,8 +513,10 @@ dsn_status ensure_batch(dsn_problem *p, int S)
             (st = alloc(&d.faceZ, n * s.face)) || (st = alloc((void **)&d.part, n * s.part)) ||
             (st = alloc((void **)&d.ctl, n * s.ctl)) || (st = alloc((void **)&d.spec, n * s.spec)) ||
             (st = alloc((void **)&d.src_par, n * kSrcPar * sizeof(double))) ||
-            (st = alloc((void **)&d.face_par, n * sizeof(int))))
+            (st = alloc((void **)&d.face_par, n * sizeof(int))) ||
+            (st = alloc((void **)&d.blk_done, n * sizeof(int))))
             return st;
+        DSN_HIP(hipMemset(d.blk_done, 0, n * sizeof(int)));
         if ((st = invalidate_faces(d, n * s.face)) != DSN_OK) return st;
         if (hipHostMalloc((void **)&d.h_ctl, n * s.ctl, hipHostMallocDefault) != hipSuccess)
             return fail(DSN_ERR_OUT_OF_MEMORY, "hipHostMalloc failed");
@@ -581,7 +545,6 @@ dsn_status ensure_combined(dsn_problem *p, int n)
 {
     dsn_status st = ensure_batch(p, 1);
     if (st != DSN_OK) return st;
-    DeviceWide gate;
     DeviceState &d = p->dev;
     if (n <= d.c_cap) return DSN_OK;
     (void)hipDeviceSynchronize();
@@ -613,7 +576,6 @@ dsn_status ensure_device(dsn_problem *p)
 {
     DeviceState &d = p->dev;
     if (d.ready) return DSN_OK;
-    DeviceWide gate;
     int n = 0;
     if (hipGetDeviceCount(&n) != hipSuccess || n == 0) return fail(DSN_ERR_DEVICE, "no HIP device available");
     int dev = 0;
@@ -714,7 +676,7 @@ SolveArgs<T> make_args(dsn_problem *p, int S = 1)
 {
     DeviceState &d = p->dev;
     SolveArgs<T> a;
-    std::memset(&a, 0, sizeof(a));  // padding too: the bytes key the iteration graphs
+    std::memset(&a, 0, sizeof(a));
     a.g = p->geom;
     a.G = p->G;
     a.L = p->L;
@@ -771,6 +733,7 @@ SolveArgs<T> make_args(dsn_problem *p, int S = 1)
     a.str_part = 4L * ((g.Vp + 255) / 256);
     a.src_par = d.src_par;
     a.face_par = d.face_par;
+    a.blk_done = d.blk_done;
     a.src_spec = d.spec;
     return a;
 }
@@ -861,11 +824,10 @@ constexpr int kFacesFused = 9, kFacesTile = 16;
 // per-XCD queues after one without, a fixed-axis recording sweep after a
 // per-XCD one), every word is invalidated on the stream, so neither codec
 // can take the other's words for its own.  Sweeps on other face buffers go
-// straight through.  Returns -1 if a switch would be needed while the stream
-// is capturing (the caller then launches without a graph).
+// straight through.
 template <typename T>
-int sweep_forward_faces(dsn_problem *p, const SolveArgs<T> &a, int g, hipStream_t s, hipEvent_t ev_before = nullptr,
-                        hipEvent_t ev_after = nullptr)
+int sweep_forward_faces(dsn_problem *p, const SolveArgs<T> &a, int g, hipStream_t s, bool follow = false,
+                        hipEvent_t ev_before = nullptr, hipEvent_t ev_after = nullptr)
 {
     DeviceState &d = p->dev;
     if ((void *)a.faceY == d.faceY) {
@@ -879,8 +841,6 @@ int sweep_forward_faces(dsn_problem *p, const SolveArgs<T> &a, int g, hipStream_
             tagged += kFacesTile + 2 * (ty + 32 * tz);
         }
         if (d.face_tagged >= 0 && tagged != d.face_tagged) {
-            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-            if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return -1;
             const size_t bytes = (size_t)d.S_cap_alloc * sizes_of(p).face;
             (void)hipMemsetAsync(d.faceY, 0xFF, bytes, s);
             (void)hipMemsetAsync(d.faceZ, 0xFF, bytes, s);
@@ -888,59 +848,7 @@ int sweep_forward_faces(dsn_problem *p, const SolveArgs<T> &a, int g, hipStream_
         }
         d.face_tagged = tagged;
     }
-    return launch_sweeps<T>(a, g, s, ev_before, ev_after);
-}
-
-// The steady source iteration of group g as a HIP graph: captured once on a
-// private stream (default priority) and replayed on the caller's stream.  All
-// state the kernels keep between launches (tickets, sweep epoch, face
-// parity, control blocks) lives in device memory, so replays are exact.
-// Returns nullptr when capture is not available (the caller launches
-// directly).
-template <typename T>
-hipGraphExec_t iteration_graph(dsn_problem *p, const SolveArgs<T> &a, int g)
-{
-    DeviceState &d = p->dev;
-    std::vector<unsigned char> key(sizeof(SolveArgs<T>) + 3 * sizeof(int));
-    std::memcpy(key.data(), &a, sizeof(SolveArgs<T>));
-    const int extra[3] = {g, p->fixup, (int)sizeof(T)};
-    std::memcpy(key.data() + sizeof(SolveArgs<T>), extra, sizeof(extra));
-    for (size_t i = 0; i < d.graphs.size(); ++i)
-        if (d.graphs[i].key == key) {
-            IterGraph x = d.graphs[i];
-            d.graphs.erase(d.graphs.begin() + i);
-            d.graphs.push_back(x);
-            return x.exec;
-        }
-    if (!d.capture && hipStreamCreateWithFlags(&d.capture, hipStreamNonBlocking) != hipSuccess) {
-        d.capture = nullptr;
-        return nullptr;
-    }
-    std::shared_lock<std::shared_mutex> lk(g_capture_gate, std::defer_lock);
-    if (t_gate_depth == 0) lk.lock();
-    hipGraph_t graph = nullptr;
-    if (hipStreamBeginCapture(d.capture, hipStreamCaptureModeThreadLocal) != hipSuccess) return nullptr;
-    const bool same_faces = sweep_forward_faces<T>(p, a, g, d.capture) >= 0;
-    launch_d2m<T>(a, g, true, d.capture);
-    const hipError_t ec = hipStreamEndCapture(d.capture, &graph);
-    if (!same_faces) {
-        if (graph) (void)hipGraphDestroy(graph);
-        return nullptr;
-    }
-    hipGraphExec_t exec = nullptr;
-    const hipError_t ei = ec == hipSuccess ? hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) : ec;
-    if (graph) (void)hipGraphDestroy(graph);
-    if (ei != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    constexpr size_t kMaxGraphs = 64;
-    if (d.graphs.size() == kMaxGraphs) {
-        (void)hipGraphExecDestroy(d.graphs.front().exec);
-        d.graphs.erase(d.graphs.begin());
-    }
-    d.graphs.push_back(IterGraph{key, exec});
-    return exec;
+    return launch_sweeps<T>(a, g, s, follow, ev_before, ev_after);
 }
 
 // Times the sweep's launch shapes on the current group's source and keeps the
@@ -1064,10 +972,12 @@ void tune_sweep(dsn_problem *p, SolveArgs<T> &a, int g, hipStream_t s)
 
 template <typename T>
 // One source iteration: sweep, then moments, residual and - while the
-// moments are in registers - the next iteration's directional source.  The
-// first iteration of a group forms its source from the moments on entry.
-// Without the stage timer the steady iterations are graph replays.  A pending
-// autotune runs at the first iteration, between the source and the sweep.
+// moments are in registers - the next iteration's directional source: two
+// launches, which the host makes faster than it replays a graph of them (16^3 S4
+// solve 1.34 ms against 1.59 ms with a graph per iteration, 64x64x16 S6 G90 90
+// against 96 ms).  The first iteration of a group forms its source from the
+// moments on entry.  A pending autotune runs at the first iteration, between
+// the source and the sweep.
 // formed: the group source kernel already wrote the first directional source.
 void enqueue_iteration(dsn_problem *p, SolveArgs<T> &a, int g, bool first, bool formed, hipStream_t s)
 {
@@ -1075,10 +985,6 @@ void enqueue_iteration(dsn_problem *p, SolveArgs<T> &a, int g, bool first, bool 
     size_t e;
     int n;
     t.cur_iter = first ? 0 : t.cur_iter + 1;
-    if (!first && !t.on) {
-        hipGraphExec_t x = iteration_graph<T>(p, a, g);
-        if (x && hipGraphLaunch(x, s) == hipSuccess) return;
-    }
     if (first) {
         if (!formed) {
             e = t.begin();
@@ -1088,10 +994,10 @@ void enqueue_iteration(dsn_problem *p, SolveArgs<T> &a, int g, bool first, bool 
         if (p->dev.tune_pending) tune_sweep<T>(p, a, g, s);
     }
     // the sweep stage times the sweep kernel alone (events recorded around
-    // its launch, after the ticket reset and before the parity flip)
+    // its launch)
     hipEvent_t eb = nullptr, ee = nullptr;
     t.pair(DSN_STAGE_SWEEP, 1, eb, ee);
-    sweep_forward_faces<T>(p, a, g, s, eb, ee);
+    sweep_forward_faces<T>(p, a, g, s, true, eb, ee);
     e = t.begin();
     n = launch_d2m<T>(a, g, true, s);
     t.end(DSN_STAGE_D2M, e, n);
@@ -1100,7 +1006,7 @@ void enqueue_iteration(dsn_problem *p, SolveArgs<T> &a, int g, bool first, bool 
 // Runs one group's source iteration to convergence (or its fixed count).
 // Iterations are enqueued in chunks between host checks of the control
 // blocks; the stage timer drops the ones that found their group converged.
-// rule: the stop rule of the group's test (see k_resid).
+// rule: the stop rule of the group's test (see resid_body).
 template <typename T>
 dsn_status iterate_group(dsn_problem *p, SolveArgs<T> &a, int g, const dsn_solve_opts &o, hipStream_t s,
                          int &chunk_hint, bool formed, int rule)
@@ -1267,9 +1173,8 @@ dsn_status solve_sources(dsn_problem *p, const dsn_source *src, int32_t n_src, c
 // batch iterates the same group in lockstep on one stream, and each source
 // iteration is one sweep launch over every (problem, source) pair - the
 // problems' argument blocks in a device table, their tickets merged diagonal
-// by diagonal - followed by one moments launch and one convergence-test
-// launch over every pair (the same tables), the whole iteration replayed as
-// one HIP graph.  A problem whose sources' group has
+// by diagonal - followed by one moments launch (with the convergence tests)
+// over every pair (the same tables).  A problem whose sources' group has
 // converged leaves the later launches of that group at once, as in a single
 // solve.  Results equal those of the problems solved one by one (the same
 // kernels and arithmetic; the launch shape changes no result).
@@ -1407,20 +1312,20 @@ dsn_status fused_round(dsn_problem *const *probs, int32_t n_probs, const dsn_sou
         return DSN_OK;
     };
     if ((st = set_shape(W, sweep_grid_multi<T>(W, mode, n_cu))) != DSN_OK) return st;
-    auto sweep_all = [&](int g, hipStream_t on, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) {
-        launch_sweep_multi<T>(M, tab.data(), n, g, on, e0, e1);
+    auto sweep_all = [&](int g, bool follow, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) {
+        launch_sweep_multi<T>(M, tab.data(), n, g, s, follow, e0, e1);
     };
     // one source iteration: the fused sweep, then the moments and the
-    // convergence test of every (problem, source) pair, two more launches
+    // convergence test of every (problem, source) pair, one more launch
     long vp_max = 0;
     int s_max = 0;
     for (int q = 0; q < n; ++q) {
         vp_max = std::max(vp_max, tab[q].g.Vp);
         s_max = std::max(s_max, tab[q].S);
     }
-    auto unit = [&](int g, hipStream_t on) {
-        sweep_all(g, on);
-        launch_d2m_multi<T>(M.multi, tab[0], n, vp_max, s_max, M.stream_nt != 0, g, on);
+    auto unit = [&](int g) {
+        sweep_all(g, true);
+        launch_d2m_multi<T>(M.multi, M, n, vp_max, s_max, g, s);
     };
     // the fused sweep's launch shape: every built waves-per-block value that
     // divides the directions of an octant, full, 3/4 and 1/2 resident grid,
@@ -1447,7 +1352,7 @@ dsn_status fused_round(dsn_problem *const *probs, int32_t n_probs, const dsn_sou
                 float tot = 0.f;
                 for (int r = 0; r < 3; ++r) {
                     for (int q = 0; q < n; ++q) launch_m2d<T>(tab[q], g, s);
-                    sweep_all(g, s, ev[0], ev[1]);
+                    sweep_all(g, false, ev[0], ev[1]);
                     DSN_HIP(hipEventSynchronize(ev[1]));
                     float ms = 0.f;
                     DSN_HIP(hipEventElapsedTime(&ms, ev[0], ev[1]));
@@ -1466,40 +1371,6 @@ dsn_status fused_round(dsn_problem *const *probs, int32_t n_probs, const dsn_sou
         for (int q = 0; q < n; ++q) launch_m2d<T>(tab[q], g, s);
         return set_shape(bw, bg);
     };
-    // the steady iteration of group g as one graph (direct launches if
-    // capture is not available)
-    hipStream_t cap = nullptr;
-    std::vector<hipGraphExec_t> graphs;
-    struct GraphsGuard {
-        std::vector<hipGraphExec_t> &g;
-        hipStream_t &c;
-        ~GraphsGuard()
-        {
-            for (hipGraphExec_t x : g) (void)hipGraphExecDestroy(x);
-            if (c) (void)hipStreamDestroy(c);
-        }
-    } graphs_guard{graphs, cap};
-    auto graph_of = [&](int g) -> hipGraphExec_t {
-        if (!cap && hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) != hipSuccess) {
-            cap = nullptr;
-            return nullptr;
-        }
-        std::shared_lock<std::shared_mutex> lk(g_capture_gate, std::defer_lock);
-        if (t_gate_depth == 0) lk.lock();
-        hipGraph_t graph = nullptr;
-        if (hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) return nullptr;
-        unit(g, cap);
-        const hipError_t ec = hipStreamEndCapture(cap, &graph);
-        hipGraphExec_t exec = nullptr;
-        const hipError_t ei = ec == hipSuccess ? hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) : ec;
-        if (graph) (void)hipGraphDestroy(graph);
-        if (ei != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        graphs.push_back(exec);
-        return exec;
-    };
     int chunk_hint = 4;
     std::vector<Ctl> hc;
     for (int g = 0; g < G; ++g) {
@@ -1511,12 +1382,8 @@ dsn_status fused_round(dsn_problem *const *probs, int32_t n_probs, const dsn_sou
         }
         if (g == 0 && tune_shape && (st = tune(g)) != DSN_OK) return st;
         DSN_HIP(hipGetLastError());
-        hipGraphExec_t gx = nullptr;
         auto enqueue = [&](int count) {
-            for (int c = 0; c < count; ++c) {
-                if (!gx) gx = graph_of(g);
-                if (!gx || hipGraphLaunch(gx, s) != hipSuccess) unit(g, s);
-            }
+            for (int c = 0; c < count; ++c) unit(g);
         };
         if (target >= 0) {
             enqueue(target);
@@ -1582,7 +1449,6 @@ dsn_status fused_round(dsn_problem *const *probs, int32_t n_probs, const dsn_sou
 // sources asked for, by the next call that needs them).
 void release_sources(dsn_problem *p)
 {
-    DeviceWide gate;
     DeviceState &d = p->dev;
     if (d.src_allocs.empty()) return;
     (void)hipDeviceSynchronize();
@@ -1704,7 +1570,6 @@ dsn_status ensure_adjoint(dsn_problem *p)
         if ((st = dev_alloc(d, (void **)&d.mask, (size_t)p->Nd * p->geom.Vp)) != DSN_OK) return st;
         if ((st = dev_alloc(d, &d.afaceY, s.face)) != DSN_OK) return st;
         if ((st = dev_alloc(d, &d.afaceZ, s.face)) != DSN_OK) return st;
-        DeviceWide gate;
         DSN_HIP(hipMemset(d.afaceY, 0xFF, s.face));
         DSN_HIP(hipMemset(d.afaceZ, 0xFF, s.face));
         DSN_HIP(hipDeviceSynchronize());
@@ -1930,6 +1795,7 @@ SolveArgs<T> carve_args(dsn_problem *p, Carve &c, int wpb, int relay, int grid, 
     a.part = c.take<double>(z.part);
     a.ctl = c.take<Ctl>(z.ctl);
     a.sweep_ctr = c.take<int>(kCtrInts * sizeof(int));
+    a.blk_done = a.sweep_ctr + (kCtrInts - 1);  // (base null: never used)
     a.sweep_dstart = c.take<int>(((size_t)g.NJ + g.NK + 1) * sizeof(int));
     a.face_par = c.take<int>(sizeof(int));
     a.src_par = c.take<double>(kSrcPar * sizeof(double));
@@ -2039,7 +1905,7 @@ dsn_status solve_noalloc(dsn_problem *p, const dsn_source &src, const dsn_solve_
                         o.stop_rule, s);
         if (target >= 0) {
             for (int it = 0; it < target; ++it) {
-                launch_sweeps<T>(a, g, s);
+                launch_sweeps<T>(a, g, s, true);
                 launch_d2m<T>(a, g, true, s);
             }
         } else {
@@ -2048,7 +1914,7 @@ dsn_status solve_noalloc(dsn_problem *p, const dsn_source &src, const dsn_solve_
             int enq = 0, chunk = 4;
             for (;;) {
                 for (int k = 0; k < chunk; ++k) {
-                    launch_sweeps<T>(a, g, s);
+                    launch_sweeps<T>(a, g, s, true);
                     launch_d2m<T>(a, g, true, s);
                 }
                 enq += chunk;
@@ -2290,10 +2156,7 @@ dsn_status dsn_create(const dsn_problem_desc *d, dsn_problem **out)
 void dsn_destroy(dsn_problem *p)
 {
     if (!p) return;
-    {
-        DeviceWide gate;
-        if (p->dev.device >= 0) (void)hipDeviceSynchronize();
-    }
+    if (p->dev.device >= 0) (void)hipDeviceSynchronize();
     dev_release(p->dev);
     delete p;
 }
@@ -2483,7 +2346,6 @@ dsn_status dsn_set_density(dsn_problem *p, const double *density)
         p->has_density = true;
         launch_voxels_to_pencils(p->geom, d.mat_nat, d.dens_nat, d.mat, d.dens, 0);
         DSN_HIP(hipGetLastError());
-        DeviceWide gate;
         DSN_HIP(hipDeviceSynchronize());
         return DSN_OK;
     } catch (...) {
@@ -2530,7 +2392,6 @@ dsn_status dsn_solve_batch(dsn_problem *const *probs, int32_t n_probs, const dsn
         if (opts->batch_mode == 1) {
             const std::string why = fused_obstacle(probs, n_probs, n_src);
             if (!why.empty()) return fail(DSN_ERR_UNSUPPORTED, "fused batch: " + why);
-            DeviceWide gate;
             hipStream_t sf = (hipStream_t)opts->stream;
             const dsn_status st = p0->precision == DSN_FP32
                                       ? solve_batch_fused<float>(probs, n_probs, srcs, n_src, *opts, phi_total, info, sf)

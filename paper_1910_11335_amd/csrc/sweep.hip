@@ -188,7 +188,6 @@ constexpr int kVolatileSC1 = (int)0x80000010u;
 constexpr int kSC0 = 1;                  // bypasses the CU's L1, coherent in the XCD's L2
 constexpr int kVolatileSC0 = (int)0x80000001u;
 constexpr int kNT = 2;                   // non-temporal: streamed data, not kept in the caches
-constexpr int kQueueCtr = 4;             // first per-XCD ticket counter in the counter block
 
 __device__ __forceinline__ Rsrc make_rsrc(const void *base, unsigned bytes)
 {
@@ -464,7 +463,7 @@ __device__ __forceinline__ void sweep_body(const SolveArgs<T> &a0, int g)
     // is past the end), [1] abort flag for the host, [2] epoch, [kQueueCtr +
     // q] next ticket of XCD q's queue
     int *const ctr = a0.sweep_ctr;
-    const unsigned epoch = (unsigned)ctr[2];  // written by k_sweep_reset before this launch
+    const unsigned epoch = (unsigned)ctr[2];  // set after the sweep before this one
     const int nq = XCD ? a0.sweep_xcd : 1;
     const int xq = XCD ? (int)__builtin_amdgcn_readfirstlane(__builtin_amdgcn_s_getreg((3 << 11) | 20)) % nq : 0;
     int *const tctr = XCD ? &ctr[kQueueCtr + xq] : &ctr[0];  // this block's ticket counter
@@ -1265,16 +1264,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     if (!good) abort_all();
 }
 
-// Before every sweep: ticket counter back to zero and the next epoch for the
-// tagged face words, kept in [1, 2^31 - 1] (invalidated words hold all ones).
-// Both live in device memory, so a captured graph replays correctly.
-__global__ void k_sweep_reset(int *ctr)
+// After a sweep that no moments pass follows (which does the same): the
+// counter block ready for the next sweep (sweep_counters_next) and, for
+// sign-parity faces, the parity of every source that ran (its group had not
+// converged) flipped, so that its next sweep rejects these words.
+__global__ void k_sweep_after(int *ctr, const Ctl *ctl, int G, int g, int S, int *par, int flip)
 {
-    if (blockIdx.x == 0 && threadIdx.x < 8) ctr[kQueueCtr + threadIdx.x] = 0;  // per-XCD queues
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        ctr[0] = 0;
-        ctr[2] = (int)((unsigned)ctr[2] % 0x7FFFFFFEu + 1u);
-    }
+    const int s = threadIdx.x;
+    sweep_counters_next(ctr, s);
+    if (flip && s < S && !ctl[(long)s * G + g].done) par[s] ^= 1;
 }
 
 // The XCD each workgroup runs on (hardware register XCC_ID), for the
@@ -1309,15 +1307,6 @@ __global__ void k_xcd_drained(const Ctl *ctl, int G, int g, int S, int *ctr, int
     for (int q = 0; q < nq; ++q) drained = drained && ctr[kQueueCtr + q] >= nitems_q;
     if (live && !drained) ctr[1] = 2;
 }
-
-// After a sweep with sign-parity faces: flip the parity of every source that
-// ran (its group had not converged), so its next sweep rejects these words.
-__global__ void k_face_parity_flip(const Ctl *ctl, int G, int g, int S, int *par)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < S && !ctl[(long)s * G + g].done) par[s] ^= 1;
-}
-
 
 // Default waves per block (directions of one octant that share a pencil
 // item); the runtime may pick another divisor of D by timing.
@@ -1540,15 +1529,15 @@ int sweep_grid_multi(int wpb, int mode, int n_cu)
 }
 
 // One sweep over every (problem, source) pair of a fused batch: a.multi (device
-// copy of host_tab) and a.seg set, a.sweep_ctr the batch's own counter block;
-// then each problem's face parity flips for its sources that ran.
+// copy of host_tab) and a.seg set, a.sweep_ctr the batch's own counter block.
+// follow: the batch's moments pass comes next; else the counters and each
+// problem's face parity are made ready for the next sweep here.
 template <typename T>
-int launch_sweep_multi(const SolveArgs<T> &a, const SolveArgs<T> *host_tab, int n, int g, hipStream_t s,
+int launch_sweep_multi(const SolveArgs<T> &a, const SolveArgs<T> *host_tab, int n, int g, hipStream_t s, bool follow,
                        hipEvent_t ev_before, hipEvent_t ev_after)
 {
     const void *f = sweep_kernel_multi<T>(a.sweep_wpb, a.sweep_mode, a.sig_from_mat != 0, a.stream_nt != 0);
     if (!f) return 0;
-    hipLaunchKernelGGL(k_sweep_reset, dim3(1), dim3(64), 0, s, a.sweep_ctr);
     SolveArgs<T> arg = a;
     int gi = g;
     void *params[2] = {&arg, &gi};
@@ -1556,11 +1545,11 @@ int launch_sweep_multi(const SolveArgs<T> &a, const SolveArgs<T> *host_tab, int 
     if (ev_before) (void)hipEventRecord(ev_before, s);
     (void)hipLaunchKernel(f, dim3(grid), dim3(64 * a.sweep_wpb), params, 0, s);
     if (ev_after) (void)hipEventRecord(ev_after, s);
-    if (a.sweep_mode == kFixup)
+    if (!follow)
         for (int q = 0; q < n; ++q) {
             const SolveArgs<T> &b = host_tab[q];
-            hipLaunchKernelGGL(k_face_parity_flip, dim3((b.S + 63) / 64), dim3(64), 0, s, b.ctl, b.G, g, b.S,
-                               b.face_par);
+            hipLaunchKernelGGL(k_sweep_after, dim3(1), dim3(64), 0, s, a.sweep_ctr, b.ctl, b.G, g, b.S, b.face_par,
+                               a.sweep_mode == kFixup);
         }
     return 1;
 }
@@ -1605,11 +1594,19 @@ int sweep_grid(int wpb, int mode, int n_cu)
     return per_cu * n_cu;
 }
 
-// Launches the sweep in cell mode a.sweep_mode with a.sweep_wpb waves per
-// block (one of the built choices; the runtime never passes another) between
-// the ticket reset and, for sign-parity faces, the parity flip.
+// Whether a sweep with these arguments leaves sign-parity face words.
 template <typename T>
-int launch_sweeps(const SolveArgs<T> &a, int g, hipStream_t s, hipEvent_t ev_before, hipEvent_t ev_after)
+bool sweep_flips_parity(const SolveArgs<T> &a)
+{
+    return !sweep_tagged_faces(sizeof(T) == 8, a.sweep_mode, a.sweep_wpb, a.sweep_relay > 0 ? 0 : a.sweep_xcd);
+}
+
+// Launches the sweep in cell mode a.sweep_mode with a.sweep_wpb waves per
+// block (one of the built choices; the runtime never passes another).
+// follow: the moments pass of this sweep comes next on the stream and makes the
+// counters and the face parity ready for the next sweep, else they are here.
+template <typename T>
+int launch_sweeps(const SolveArgs<T> &a, int g, hipStream_t s, bool follow, hipEvent_t ev_before, hipEvent_t ev_after)
 {
     // tile items, per-XCD queues where such a kernel is built (FP32 fixup
     // sweeps), else pencil items on the global queue
@@ -1620,7 +1617,6 @@ int launch_sweeps(const SolveArgs<T> &a, int g, hipStream_t s, hipEvent_t ev_bef
                     : xcd ? sweep_kernel_xcd<T>(a.sweep_wpb, a.sweep_mode, a.sig_from_mat != 0, nt)
                           : sweep_kernel_of<T>(a.sweep_wpb, a.sweep_mode, a.sig_from_mat != 0, nt);
     if (!f) return 0;
-    hipLaunchKernelGGL(k_sweep_reset, dim3(1), dim3(64), 0, s, a.sweep_ctr);
     unsigned grid = (unsigned)(a.sweep_grid < a.sweep_nitems ? a.sweep_grid : a.sweep_nitems);
     if (xcd)  // a whole number of blocks per XCD, at least one each
         grid = (grid + a.sweep_xcd - 1) / a.sweep_xcd * a.sweep_xcd;
@@ -1638,8 +1634,9 @@ int launch_sweeps(const SolveArgs<T> &a, int g, hipStream_t s, hipEvent_t ev_bef
     if (xcd)
         hipLaunchKernelGGL(k_xcd_drained, dim3(1), dim3(64), 0, s, a.ctl, a.G, g, a.S, a.sweep_ctr, a.sweep_xcd,
                            a.sweep_nitems / a.sweep_xcd);
-    else if (a.sweep_mode == kFixup || a.sweep_mode == kRecord)
-        hipLaunchKernelGGL(k_face_parity_flip, dim3((a.S + 63) / 64), dim3(64), 0, s, a.ctl, a.G, g, a.S, a.face_par);
+    if (!follow)
+        hipLaunchKernelGGL(k_sweep_after, dim3(1), dim3(64), 0, s, a.sweep_ctr, a.ctl, a.G, g, a.S, a.face_par,
+                           sweep_flips_parity(a) ? 1 : 0);
     return 1;
 }
 
@@ -1657,13 +1654,15 @@ template int sweep_grid<float>(int, int, int);
 template int sweep_grid<double>(int, int, int);
 template int sweep_grid_tile<float>(int, int, int, int, int);
 template int sweep_grid_tile<double>(int, int, int, int, int);
-template int launch_sweeps<float>(const SolveArgs<float> &, int, hipStream_t, hipEvent_t, hipEvent_t);
-template int launch_sweeps<double>(const SolveArgs<double> &, int, hipStream_t, hipEvent_t, hipEvent_t);
+template int launch_sweeps<float>(const SolveArgs<float> &, int, hipStream_t, bool, hipEvent_t, hipEvent_t);
+template int launch_sweeps<double>(const SolveArgs<double> &, int, hipStream_t, bool, hipEvent_t, hipEvent_t);
+template bool sweep_flips_parity<float>(const SolveArgs<float> &);
+template bool sweep_flips_parity<double>(const SolveArgs<double> &);
 template int sweep_grid_multi<float>(int, int, int);
 template int sweep_grid_multi<double>(int, int, int);
-template int launch_sweep_multi<float>(const SolveArgs<float> &, const SolveArgs<float> *, int, int, hipStream_t,
+template int launch_sweep_multi<float>(const SolveArgs<float> &, const SolveArgs<float> *, int, int, hipStream_t, bool,
                                        hipEvent_t, hipEvent_t);
-template int launch_sweep_multi<double>(const SolveArgs<double> &, const SolveArgs<double> *, int, int, hipStream_t,
+template int launch_sweep_multi<double>(const SolveArgs<double> &, const SolveArgs<double> *, int, int, hipStream_t, bool,
                                         hipEvent_t, hipEvent_t);
 
 }  // namespace dsn
