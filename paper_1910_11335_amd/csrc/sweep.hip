@@ -296,7 +296,7 @@ struct SignFace<float> {
     }
     static __device__ __forceinline__ bool ok(Word w, unsigned parity)
     {
-        return (w >> 31) == parity && (w & 0x7FFFFFFFu) <= 0x7F800000u;
+        return (w ^ (parity << 31)) <= 0x7F800000u;  // the parity bit matches and the rest is no NaN
     }
     static __device__ __forceinline__ float value(Word w) { return __uint_as_float(w & 0x7FFFFFFFu); }
     template <int AUX>
@@ -950,7 +950,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     const bool tells = lane < 2 || (lane == 2 && ja > 0) || (lane == 3 && ka > 0);
     const bool inY = ja > 0, inZ = ka > 0;  // inflow from the team's neighbour (a link)
     int done = 0;
-    int spy = 0, spz = 0, scy = 0, scz = 0;  // the next ring slots
+    int slot = 0;  // the next ring slot of the lane's link
     const int jr = lane & 7, kr = lane >> 3;
     const int skew = jr + kr;
     const int srcZ = ((lane - 8) & 63) << 2;
@@ -1053,15 +1053,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
         const int cnext = nchunks > 3 ? nchunks - 3 : 0;
         const int pstep = sx * RB;
         int poff = (sx > 0 ? 0 : (nx - 1) * RB) + (lrow - ph) * pstep + lcol * 16;  // next chunk's rows, this lane
-        // face words: entry e's word of step u (row u - skew) sits in slot
-        // u mod nx; this lane moves step ro of a chunk
+        // Face words: this lane moves the words of entry e at step ro of a
+        // chunk, i.e. of row u - skew at step u along the face.  They sit in
+        // slot u, from slot 0 on again past the end (below 8 rows: in slot
+        // row).  Tracked: the rows of the next chunk's inflow words.
         const int skY = sz > 0 ? e : 7 - e, skZ = sy > 0 ? e : 7 - e;
-        int uin = ro - ph;  // the next chunk's inflow step of this lane
+        const bool wrap = nx >= 8;
+        int rowY = ro - ph - skY, rowZ = ro - ph - skZ;
+        const int thrY = wrap ? nx - skY : nx, thrZ = wrap ? nx - skZ : nx;  // first row of the wrapped part
+        const unsigned fcY = (unsigned)((wrap ? skY : 0) * FB + e * (int)Face::BYTES);
+        const unsigned fcZ = (unsigned)((wrap ? skZ : 0) * FB + e * (int)Face::BYTES);
         const bool pY = !outY && Jr < NJ - 1, pZ = !outZ && Kr < NK - 1;  // outflow to memory
-        auto face_off = [&](int u_, int sk, unsigned base) -> unsigned {
-            int slot = u_ < nx ? u_ : u_ - nx;
-            if (nx < 8) slot = u_ % nx;
-            return (unsigned)(u_ - sk) < (unsigned)nx ? base + (unsigned)(slot * FB + e * (int)Face::BYTES) : kNone;
+        auto face_off = [&](int row, int thr, unsigned fc) -> unsigned {
+            const unsigned o_ = (unsigned)row * FB + fc - (row >= thr ? fpen : 0u);
+            return (unsigned)row < (unsigned)nx ? o_ : kNone;
         };
         constexpr int SR = Sig::ROW;
         const int sstep = sx * SR;
@@ -1079,8 +1084,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
 #pragma unroll
             for (int i = 0; i < NI; ++i)
                 pq[i] = __builtin_amdgcn_raw_buffer_load_b128(rPsi, (unsigned)(poff + i * RI * pstep), 0, kPsiAux);
-            if (gY) offy = face_off(uin, skY, inYo);
-            if (gZ) offz = face_off(uin, skZ, inZo);
+            if (gY) offy = face_off(rowY, thrY, fcY + inYo);
+            if (gZ) offz = face_off(rowZ, thrZ, fcZ + inZo);
             Face::template load<kSC1>(pfy, rFY, offy);
             Face::template load<kSC1>(pfz, rFZ, offz);
             if constexpr (SM) {
@@ -1091,10 +1096,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
         };
         // the outflow words of one chunk (dropped off the tile's rim): what
         // its step b made is used downstream at step b - 7
-        auto put_faces = [&](int uo) {
+        auto put_faces = [&](int back, int spy, int spz) {  // of the chunk that starts `back` rows before rowY, rowZ
             unsigned oy_ = kNone, oz_ = kNone;
-            if (pY) oy_ = face_off(uo, skY, ownYo);
-            if (pZ) oz_ = face_off(uo, skZ, ownZo);
+            if (pY) oy_ = face_off(rowY - back - 7, thrY, fcY + ownYo);
+            if (pZ) oz_ = face_off(rowZ - back - 7, thrZ, fcZ + ownZo);
             Face::template put<kSC1>(rFY, oy_, sF[w][2 + spy][e][ro], stamp);
             Face::template put<kSC1>(rFZ, oz_, sF[w][2 + NS + spz][e][ro], stamp);
         };
@@ -1113,26 +1118,34 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
                 *(U32x2 *)&sMt[w][q0 + mat_row(sx, lane)][8 * (lane & 7)] =
                     U32x2{(pmt[0] & 0x1F1F1F1Fu) << kSh, (pmt[1] & 0x1F1F1F1Fu) << kSh};
             }
-            bool okY = offy == kNone || Face::ok(pfy, stamp);
-            bool okZ = offz == kNone || Face::ok(pfz, stamp);
-            int spins = 0;
-            while (good && __any(!(okY && okZ))) {
-                __builtin_amdgcn_s_sleep(1);
-                if (!okY) {
-                    Face::template load<kVolatileSC1>(pfy, rFY, offy);
-                    okY = Face::ok(pfy, stamp);
+            if (gY || gZ) {
+                bool okY = !gY || offy == kNone || Face::ok(pfy, stamp);
+                bool okZ = !gZ || offz == kNone || Face::ok(pfz, stamp);
+                int spins = 0;
+                while (good && __any(!(okY && okZ))) {
+                    __builtin_amdgcn_s_sleep(1);
+                    if (!okY) {
+                        Face::template load<kVolatileSC1>(pfy, rFY, offy);
+                        okY = Face::ok(pfy, stamp);
+                    }
+                    if (!okZ) {
+                        Face::template load<kVolatileSC1>(pfz, rFZ, offz);
+                        okZ = Face::ok(pfz, stamp);
+                    }
+                    good = !gave_up(++spins, a0.sweep_spin_limit);
                 }
-                if (!okZ) {
-                    Face::template load<kVolatileSC1>(pfz, rFZ, offz);
-                    okZ = Face::ok(pfz, stamp);
-                }
-                good = !gave_up(++spins, a0.sweep_spin_limit);
+                if (gY) sF[w][0][e][ro] = Face::value(pfy);
+                if (gZ) sF[w][1][e][ro] = Face::value(pfz);
             }
-            sF[w][0][e][ro] = Face::value(pfy);
-            sF[w][1][e][ro] = Face::value(pfz);
         };
         T px = T(0), oy = T(0), oz = T(0);
-        int s0 = skew ? RQ - skew : 0;  // ring slot of the lane's row at the next chunk's step 0
+        // ring slot of the lane's row at the next chunk's step 0; its psi (and
+        // material) entry there, and where slot 0 follows slot RQ - 1: entry b
+        // of a chunk is b rows on from one of the two, so a step's address is
+        // one select and an immediate offset
+        int s0 = skew ? RQ - skew : 0;
+        char *const qcol = (char *)&sQ[w][0][pl];
+        unsigned char *const mcol = &sMt[SM ? w : 0][0][SM ? pl : 0];
 
         // rows -14 .. -1 (and two slots more): zero source, zero sigma
 #pragma unroll
@@ -1142,6 +1155,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
             ((U4 *)&sMt[w][RQ - 16][0])[lane] = U4{kZ, kZ, kZ, kZ};
         }
         load_rows(-ph);
+        if (!gY) sF[w][0][e][ro] = T(0);  // the mesh boundary
+        if (!gZ) sF[w][1][e][ro] = T(0);
         __builtin_amdgcn_sched_barrier(0);
         {
             int so = sig_off(-skew);
@@ -1159,7 +1174,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
         // all out of range: only mirrors the loop's issue order, so that the
         // wait at the loop's head can leave the newest stores in flight
         put_rows(0);
-        put_faces(-64);
+        put_faces(64, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         int q0 = 0;  // ring slot of the chunk's first new row
         // chunks c in [link_lo, link_hi) count on this lane's link
@@ -1172,24 +1187,31 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
         for (int c = 0; good && c < nchunks; ++c) {
             commit(q0);
             // this chunk's own inputs from the rings
-            int sq[CH];
             T q[CH], sg[CH];
+            char *qb[CH];
+            {
+                char *const qa = qcol + s0 * RB, *const qw_ = qa - RQ * RB;
+                const unsigned char *const ma = mcol + s0 * 64, *const mw = ma - RQ * 64;
 #pragma unroll
-            for (int b = 0; b < CH; ++b) {
-                sq[b] = s0 + b < RQ ? s0 + b : s0 + b - RQ;
-                q[b] = sQ[w][sq[b]][pl];
-                if constexpr (SM) sg[b] = *(const T *)((const char *)sSigT + sMt[w][sq[b]][pl]);
+                for (int b = 0; b < CH; ++b) {
+                    const bool in = s0 < RQ - b;
+                    qb[b] = in ? qa : qw_;
+                    q[b] = *(const T *)(qb[b] + b * RB);
+                    if constexpr (SM) sg[b] = *(const T *)((const char *)sSigT + (in ? ma : mw)[b * 64]);
+                }
             }
             if (c == cnext && tw == 0 && !once) {
                 if (lane == 0) tnext = atomicAdd(&ctr[opaque0], 1);
                 have_next = true;
             }
-            const int uo = uin - 7;
             poff += CH * pstep;
-            uin += CH;
+            rowY += CH;
+            rowZ += CH;
             load_rows(CH * (c + 1) - ph);
             // inflow chunks there, outflow slots free
             const int step_ = c >= link_lo && c < link_hi ? 1 : 0;
+            const int spy = __builtin_amdgcn_readlane(slot, 0), spz = __builtin_amdgcn_readlane(slot, 1);
+            const int scy = __builtin_amdgcn_readlane(slot, 2), scz = __builtin_amdgcn_readlane(slot, 3);
             const int want = done + (lane == 2 || lane == 3 ? step_ : 1 - NS);
             int spins = 0;
             while (good && __any(lds_get(watch) < want)) {
@@ -1246,17 +1268,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             if (tells) __hip_atomic_store(tell, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 #pragma unroll
-            for (int b = 0; b < CH; ++b) sQ[w][sq[b]][pl] = po[b];
+            for (int b = 0; b < CH; ++b) *(T *)(qb[b] + b * RB) = po[b];
             // psi rows 8c-16 .. 8c-9 (counted with the idle steps) are
             // complete, and go back
             const int qw = q0 == RQ - CH ? 0 : q0 + CH;
             put_rows(qw);
-            put_faces(uo);
-            const bool takes = c < nlink, gives = c >= first_out;
-            if (inY && takes) scy = scy + 1 < NS ? scy + 1 : 0;
-            if (inZ && takes) scz = scz + 1 < NS ? scz + 1 : 0;
-            if (outY && gives) spy = spy + 1 < NS ? spy + 1 : 0;
-            if (outZ && gives) spz = spz + 1 < NS ? spz + 1 : 0;
+            put_faces(CH, spy, spz);
+            slot += step_;
+            slot = slot == NS ? 0 : slot;
             q0 = qw;
             s0 = s0 + CH < RQ ? s0 + CH : s0 + CH - RQ;
         }
