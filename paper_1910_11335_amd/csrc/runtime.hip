@@ -302,12 +302,15 @@ int tile_grid_of(const DeviceState &d, int w, int r)
 // the memory does; what tells them apart is the number of rounds in which the
 // resident waves (16 a CU in FP32, 8 in FP64) sweep the pencil-directions.
 // Measured per sweep, pencil default against tile (us): 1.2 rounds (64^3 S8
-// FP32) 167 / 114, 5 rounds (128^3 S8 FP32) 439 / 382, 5.6 rounds (8 sources,
-// 48^3 S8 FP32) 215 / 217, 9 rounds (64^3 S16 FP64) 370 / 383, 18 rounds
-// (128^3 S16 FP32) 1102 / 1151.  The large tile saves hops through memory but
-// puts a direction's waves on one CU: it wins while the machine is not full
-// (64^3 S8 114 / 118, 40^3 S8 65 / 76, 20x100x30 S8 87 / 105) unless the pencils
-// are long (100x20x30 S8 78 / 71) or leave much of it idle.
+// FP32) 160 / 105, 5 rounds (128^3 S8 FP32) 439 / 368, 5.6 rounds (8 sources,
+// 48^3 S8 FP32) 209 / 207, 9 rounds (64^3 S16 FP64) 364 / 378, 18 rounds
+// (128^3 S16 FP32) 1083 / 1127.  The larger team saves hops through memory but
+// keeps a direction's waves on one CU: it wins where the waves fill the machine
+// about once anyway and the pencils are short (solves, team of 4 / larger, ms:
+// 40^3 S8 FP32 2.06 / 1.87, 48^3 S8 FP32 2.37 / 2.16, 20x100x30 S8 FP32 1.97 /
+// 1.73, 40^3 S8 FP64 4.23 / 4.05), not below (64x64x16 S6 FP32 81.8 / 86.7),
+// beyond (48^3 S8 FP64 5.09 / 5.65) or on long ones (100x20x30 S8 FP32 1.39 /
+// 1.56).
 // Problems of a batch that sweep beside this one (on other streams) fill the
 // machine too: rounds_beside counts theirs.
 double sweep_rounds(const dsn_problem *p, int S, int n_cu)
@@ -325,11 +328,8 @@ SweepShape default_shape(const dsn_problem *p, int S, int n_cu, double rounds_be
     SweepShape x;
     const double rounds = sweep_rounds(p, S, n_cu) + rounds_beside;
     if (pens > 1 && rounds < 8.0) {
-        int ty = 1, tz = 1;
-        sweep_tile(fp64, 1, 4, NJ, NK, &ty, &tz);
-        const int slots = (NJ + ty - 1) / ty * ty * ((NK + tz - 1) / tz) * tz;
         x.wpb = 1;
-        x.relay = rounds <= 1.5 && p->geom.nx <= 64 && 4 * pens >= 3 * slots ? 4 : 2;
+        x.relay = rounds >= 0.4 && rounds <= 1.25 && p->geom.nx <= 48 ? 4 : 2;
         x.blocks = tile_blocks(x.wpb, x.relay);
         if (x.blocks > 0) return x;
     }
@@ -442,7 +442,7 @@ dsn_status invalidate_faces(DeviceState &d, size_t bytes)
     DSN_HIP(hipDeviceSynchronize());
     DSN_HIP(hipMemset(d.faceY, 0xFF, bytes));
     DSN_HIP(hipMemset(d.faceZ, 0xFF, bytes));
-    DSN_HIP(hipMemset(d.face_par, 0, (size_t)d.S_cap_alloc * sizeof(int)));
+    DSN_HIP(hipMemset(d.face_par, 0, 2 * (size_t)d.S_cap_alloc * sizeof(int)));
     DSN_HIP(hipDeviceSynchronize());
     d.face_tagged = -1;
     return DSN_OK;
@@ -513,10 +513,9 @@ dsn_status ensure_batch(dsn_problem *p, int S)
             (st = alloc(&d.faceZ, n * s.face)) || (st = alloc((void **)&d.part, n * s.part)) ||
             (st = alloc((void **)&d.ctl, n * s.ctl)) || (st = alloc((void **)&d.spec, n * s.spec)) ||
             (st = alloc((void **)&d.src_par, n * kSrcPar * sizeof(double))) ||
-            (st = alloc((void **)&d.face_par, n * sizeof(int))) ||
-            (st = alloc((void **)&d.blk_done, n * sizeof(int))))
+            (st = alloc((void **)&d.face_par, 2 * n * sizeof(int))))
             return st;
-        DSN_HIP(hipMemset(d.blk_done, 0, n * sizeof(int)));
+        d.blk_done = d.face_par + n;
         if ((st = invalidate_faces(d, n * s.face)) != DSN_OK) return st;
         if (hipHostMalloc((void **)&d.h_ctl, n * s.ctl, hipHostMallocDefault) != hipSuccess)
             return fail(DSN_ERR_OUT_OF_MEMORY, "hipHostMalloc failed");

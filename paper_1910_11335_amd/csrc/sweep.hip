@@ -849,6 +849,13 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(sizeof
 // chunk at least kTileSlots behind; in the order (item, chunk + j + k) both
 // are smaller, so every wait ends.  All are bounded as in k_sweep.
 //
+// What bounds it then is one wave's own pace, about 1 us a chunk in FP32 and
+// 1.7 us with fixup passes: few waves share a SIMD, so every instruction and
+// every LDS trip of a chunk counts.  Hence one LDS trip between the steps of
+// two chunks, no branch off the common path, and addresses as immediate
+// offsets (64x64x16 S6 G90 solve 87.5 -> 81.9 ms, 40^3 S8 2.00 -> 1.87 ms).  The
+// sweep of 64^3 S8 takes 105 us (k_sweep: 146-160), in FP64 166 (202-217).
+//
 // Global rim words: word (slot, entry) of a pencil face, slot = u mod nx with
 // u = row + the entry's skew along the face: a bijection of the nx rows of
 // each entry, and a chunk's words are one contiguous run (split where it
@@ -874,7 +881,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     __shared__ __align__(16) unsigned char sMt[SM ? NW : 1][SM ? RQ : 1][64];  // SM: material byte ring (slots as sQ)
     __shared__ int sCtr[NW][4];  // per wave: y, z chunks handed over; y, z chunks its downstream waves have consumed
     __shared__ int sItem[NW][kItemRing], sPub[NW], sTaken[NW];  // tickets of the team led by the wave; items taken
-    __shared__ int sAbort;
+    __shared__ int sAbort, sSpare[NW];
     __shared__ T sSigT[SM ? kSigTab : 1];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -946,8 +953,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     const int wy = ja > 0 ? w - 1 : w, wz = ka > 0 ? w - TY : w;
     int *const own = &sCtr[0][0] + 4 * w, *const upy = &sCtr[0][0] + 4 * wy, *const upz = &sCtr[0][0] + 4 * wz;
     int *const watch = lane == 1 ? own + 3 : lane == 2 ? upy : lane == 3 ? upz + 1 : own + 2;
-    int *const tell = lane == 1 ? own + 1 : lane == 2 ? upy + 2 : lane == 3 ? upz + 3 : own;
-    const bool tells = lane < 2 || (lane == 2 && ja > 0) || (lane == 3 && ka > 0);
+    // (a count that nobody watches goes to the wave's spare word)
+    int *const tell = lane == 0 ? own : lane == 1 ? own + 1 : lane == 2 && ja > 0 ? upy + 2
+                      : lane == 3 && ka > 0 ? upz + 3 : &sSpare[w];
     const bool inY = ja > 0, inZ = ka > 0;  // inflow from the team's neighbour (a link)
     int done = 0;
     int slot = 0;  // the next ring slot of the lane's link
@@ -1050,7 +1058,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
         const int phu = (ph + 1) & 7;          // the upstream pencils' phase
         const int nlink = (nx + phu + 15) / CH + 1 - (phu > 0 ? 1 : 0);  // chunks they hand over
         const int nchunks = (nx + ph + 15) / CH + 1;
-        const int cnext = nchunks > 3 ? nchunks - 3 : 0;
+        // where the leading wave asks for the team's next ticket
+        const int cnext = tw != 0 || once ? -1 : nchunks > 3 ? nchunks - 3 : 0;
         const int pstep = sx * RB;
         int poff = (sx > 0 ? 0 : (nx - 1) * RB) + (lrow - ph) * pstep + lcol * 16;  // next chunk's rows, this lane
         // Face words: this lane moves the words of entry e at step ro of a
@@ -1064,9 +1073,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
         const unsigned fcY = (unsigned)((wrap ? skY : 0) * FB + e * (int)Face::BYTES);
         const unsigned fcZ = (unsigned)((wrap ? skZ : 0) * FB + e * (int)Face::BYTES);
         const bool pY = !outY && Jr < NJ - 1, pZ = !outZ && Kr < NK - 1;  // outflow to memory
-        auto face_off = [&](int row, int thr, unsigned fc) -> unsigned {
+        // rows that have a word in memory (none where the face is a link's or the mesh's)
+        const unsigned ninY = gY ? nx : 0, ninZ = gZ ? nx : 0, noutY = pY ? nx : 0, noutZ = pZ ? nx : 0;
+        auto face_off = [&](int row, unsigned rows, int thr, unsigned fc) -> unsigned {
             const unsigned o_ = (unsigned)row * FB + fc - (row >= thr ? fpen : 0u);
-            return (unsigned)row < (unsigned)nx ? o_ : kNone;
+            return (unsigned)row < rows ? o_ : kNone;
         };
         constexpr int SR = Sig::ROW;
         const int sstep = sx * SR;
@@ -1084,8 +1095,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
 #pragma unroll
             for (int i = 0; i < NI; ++i)
                 pq[i] = __builtin_amdgcn_raw_buffer_load_b128(rPsi, (unsigned)(poff + i * RI * pstep), 0, kPsiAux);
-            if (gY) offy = face_off(rowY, thrY, fcY + inYo);
-            if (gZ) offz = face_off(rowZ, thrZ, fcZ + inZo);
+            offy = face_off(rowY, ninY, thrY, fcY + inYo);
+            offz = face_off(rowZ, ninZ, thrZ, fcZ + inZo);
             Face::template load<kSC1>(pfy, rFY, offy);
             Face::template load<kSC1>(pfz, rFZ, offz);
             if constexpr (SM) {
@@ -1096,19 +1107,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
         };
         // the outflow words of one chunk (dropped off the tile's rim): what
         // its step b made is used downstream at step b - 7
-        auto put_faces = [&](int back, int spy, int spz) {  // of the chunk that starts `back` rows before rowY, rowZ
-            unsigned oy_ = kNone, oz_ = kNone;
-            if (pY) oy_ = face_off(rowY - back - 7, thrY, fcY + ownYo);
-            if (pZ) oz_ = face_off(rowZ - back - 7, thrZ, fcZ + ownZo);
-            Face::template put<kSC1>(rFY, oy_, sF[w][2 + spy][e][ro], stamp);
-            Face::template put<kSC1>(rFZ, oz_, sF[w][2 + NS + spz][e][ro], stamp);
+        auto put_faces = [&](int back, T fwy, T fwz) {  // of the chunk that starts `back` rows before rowY, rowZ
+            const unsigned oy_ = face_off(rowY - back - 7, noutY, thrY, fcY + ownYo);
+            const unsigned oz_ = face_off(rowZ - back - 7, noutZ, thrZ, fcZ + ownZo);
+            Face::template put<kSC1>(rFY, oy_, fwy, stamp);
+            Face::template put<kSC1>(rFZ, oz_, fwz, stamp);
         };
-        // psi rows of the ring from slot qw on, of the chunk three before poff
-        auto put_rows = [&](int qw) {
+        // psi rows of the ring from slot qw on, of the chunk four before poff
+        U4 wb[NI];
+        auto get_rows = [&](int qw) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) wb[i] = *(const U4 *)&sQ[w][qw + i * RI + lrow][lcol * VL];
+        };
+        auto put_rows = [&]() {
 #pragma unroll
             for (int i = 0; i < NI; ++i)
-                __builtin_amdgcn_raw_buffer_store_b128(*(const U4 *)&sQ[w][qw + i * RI + lrow][lcol * VL], rPsi,
-                                                       (unsigned)(poff + (i * RI - 3 * CH) * pstep), 0, kPsiAux);
+                __builtin_amdgcn_raw_buffer_store_b128(wb[i], rPsi, (unsigned)(poff + (i * RI - 4 * CH) * pstep), 0, kPsiAux);
         };
         auto commit = [&](int q0) {
 #pragma unroll
@@ -1118,25 +1132,26 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
                 *(U32x2 *)&sMt[w][q0 + mat_row(sx, lane)][8 * (lane & 7)] =
                     U32x2{(pmt[0] & 0x1F1F1F1Fu) << kSh, (pmt[1] & 0x1F1F1F1Fu) << kSh};
             }
-            if (gY || gZ) {
-                bool okY = !gY || offy == kNone || Face::ok(pfy, stamp);
-                bool okZ = !gZ || offz == kNone || Face::ok(pfz, stamp);
+            // (out of range reads as zero: the mesh boundary's inflow, and what
+            // a link leaves unused)
+            bool badY = offy != kNone & !Face::ok(pfy, stamp), badZ = offz != kNone & !Face::ok(pfz, stamp);
+            if (__builtin_expect(__any(badY | badZ), 0)) {
                 int spins = 0;
-                while (good && __any(!(okY && okZ))) {
+                do {
                     __builtin_amdgcn_s_sleep(1);
-                    if (!okY) {
+                    if (badY) {
                         Face::template load<kVolatileSC1>(pfy, rFY, offy);
-                        okY = Face::ok(pfy, stamp);
+                        badY = !Face::ok(pfy, stamp);
                     }
-                    if (!okZ) {
+                    if (badZ) {
                         Face::template load<kVolatileSC1>(pfz, rFZ, offz);
-                        okZ = Face::ok(pfz, stamp);
+                        badZ = !Face::ok(pfz, stamp);
                     }
-                    good = !gave_up(++spins, a0.sweep_spin_limit);
-                }
-                if (gY) sF[w][0][e][ro] = Face::value(pfy);
-                if (gZ) sF[w][1][e][ro] = Face::value(pfz);
+                    good = good && !gave_up(++spins, a0.sweep_spin_limit);
+                } while (good && __any(badY | badZ));
             }
+            sF[w][0][e][ro] = Face::value(pfy);
+            sF[w][1][e][ro] = Face::value(pfz);
         };
         T px = T(0), oy = T(0), oz = T(0);
         // ring slot of the lane's row at the next chunk's step 0; its psi (and
@@ -1155,8 +1170,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
             ((U4 *)&sMt[w][RQ - 16][0])[lane] = U4{kZ, kZ, kZ, kZ};
         }
         load_rows(-ph);
-        if (!gY) sF[w][0][e][ro] = T(0);  // the mesh boundary
-        if (!gZ) sF[w][1][e][ro] = T(0);
         __builtin_amdgcn_sched_barrier(0);
         {
             int so = sig_off(-skew);
@@ -1171,36 +1184,60 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        // all out of range: only mirrors the loop's issue order, so that the
-        // wait at the loop's head can leave the newest stores in flight
-        put_rows(0);
-        put_faces(64, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        int q0 = 0;  // ring slot of the chunk's first new row
         // chunks c in [link_lo, link_hi) count on this lane's link
         const int link_lo = lane == 2 || lane == 3 ? 0 : first_out;
         const int link_hi = lane == 1 ? (outZ ? nchunks : 0) : lane == 2 ? (inY ? nlink : 0)
                             : lane == 3 ? (inZ ? nlink : 0) : (outY ? nchunks : 0);
-        // one way out, at the end of the body (a chunk whose wait gave up runs
-        // on over garbage; the launch is reported as failed): with another the
-        // compiler would wait at the loop's head for the newest stores
-        for (int c = 0; good && c < nchunks; ++c) {
+        // A wave that runs alone on its SIMD waits out every LDS trip, so a
+        // chunk has one: between two chunks' steps all LDS accesses are
+        // issued in a row, each in its place (the LDS keeps a wave's order):
+        // outflow and the counter that hands it over, finished rows, new rows,
+        // the next chunk's inputs, the upstream counter and the inflow it
+        // vouches for.  Loads and stores to memory are issued behind them.
+        int q0 = 0;                    // ring slot of the chunk's first new row
+        int spy = 0, spz = 0;          // the chunk's outflow slots
+        const T *fyr, *fzr;            // its inflow
+        T q[CH], sg[CH], fy[CH], fz[CH];
+        char *qb[CH];
+        int seen;
+        // (16 waves of a block have too few registers to hold them early)
+        constexpr bool kEarly = NW <= 8;
+        auto get_inflow = [&]() {
+            seen = __hip_atomic_load(watch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int i = 0; i < CH / VL; ++i) {
+                *(U4 *)&fy[i * VL] = *(const U4 *)&fyr[i * VL];
+                *(U4 *)&fz[i * VL] = *(const U4 *)&fzr[i * VL];
+            }
+        };
+        // the inputs of chunk c out of the rings, and the loads of chunk c + 1
+        auto enter = [&](int c) {
             commit(q0);
-            // this chunk's own inputs from the rings
-            T q[CH], sg[CH];
-            char *qb[CH];
             {
                 char *const qa = qcol + s0 * RB, *const qw_ = qa - RQ * RB;
                 const unsigned char *const ma = mcol + s0 * 64, *const mw = ma - RQ * 64;
+                unsigned mb[CH];
 #pragma unroll
                 for (int b = 0; b < CH; ++b) {
                     const bool in = s0 < RQ - b;
                     qb[b] = in ? qa : qw_;
-                    q[b] = *(const T *)(qb[b] + b * RB);
-                    if constexpr (SM) sg[b] = *(const T *)((const char *)sSigT + (in ? ma : mw)[b * 64]);
+                    if constexpr (SM) mb[b] = (in ? ma : mw)[b * 64];
+                }
+#pragma unroll
+                for (int b = 0; b < CH; ++b) q[b] = *(const T *)(qb[b] + b * RB);
+                spy = __builtin_amdgcn_readlane(slot, 0);
+                spz = __builtin_amdgcn_readlane(slot, 1);
+                const int scy = __builtin_amdgcn_readlane(slot, 2), scz = __builtin_amdgcn_readlane(slot, 3);
+                fyr = inY ? sF[wy][2 + scy][kp] : sF[w][0][kp];
+                fzr = inZ ? sF[wz][2 + NS + scz][jp] : sF[w][1][jp];
+                if constexpr (kEarly) get_inflow();
+                if constexpr (SM) {
+#pragma unroll
+                    for (int b = 0; b < CH; ++b) sg[b] = *(const T *)((const char *)sSigT + mb[b]);
                 }
             }
-            if (c == cnext && tw == 0 && !once) {
+            if (__builtin_expect(c == cnext, 0)) {
                 if (lane == 0) tnext = atomicAdd(&ctr[opaque0], 1);
                 have_next = true;
             }
@@ -1208,30 +1245,34 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
             rowY += CH;
             rowZ += CH;
             load_rows(CH * (c + 1) - ph);
+        };
+        // (The stores, here all out of range, mirror the loop's issue order,
+        // so that the wait for the loads can leave the newest in flight.)
+        put_faces(64, T(0), T(0));
+        get_rows(0);
+        enter(0);
+        put_rows();
+        T inz = T(0);
+        // one way out, at the end of the body (a chunk whose wait gave up runs
+        // on over garbage; the launch is reported as failed): with another the
+        // compiler would wait in the loop for the newest stores
+        for (int c = 0; good && c < nchunks; ++c) {
             // inflow chunks there, outflow slots free
             const int step_ = c >= link_lo && c < link_hi ? 1 : 0;
-            const int spy = __builtin_amdgcn_readlane(slot, 0), spz = __builtin_amdgcn_readlane(slot, 1);
-            const int scy = __builtin_amdgcn_readlane(slot, 2), scz = __builtin_amdgcn_readlane(slot, 3);
             const int want = done + (lane == 2 || lane == 3 ? step_ : 1 - NS);
-            int spins = 0;
-            while (good && __any(lds_get(watch) < want)) {
-                __builtin_amdgcn_s_sleep(1);
-                good = !gave_up(++spins, lds_limit);
+            if constexpr (!kEarly) get_inflow();
+            if (__builtin_expect(__any(seen < want), 0)) {
+                int spins = 0;
+                do {
+                    __builtin_amdgcn_s_sleep(1);
+                    get_inflow();
+                    good = good && !gave_up(++spins, lds_limit);
+                } while (good && __any(seen < want));
             }
-            T fy[CH], fz[CH], po[CH], yo_[CH], zo_[CH];
-            {
-                const T *const fyr = inY ? sF[wy][2 + scy][kp] : sF[w][0][kp];
-                const T *const fzr = inZ ? sF[wz][2 + NS + scz][jp] : sF[w][1][jp];
-#pragma unroll
-                for (int i = 0; i < CH / VL; ++i) {
-                    *(U4 *)&fy[i * VL] = *(const U4 *)&fyr[i * VL];
-                    *(U4 *)&fz[i * VL] = *(const U4 *)&fzr[i * VL];
-                }
-            }
+            T po[CH], yo_[CH], zo_[CH];
             const int ir0 = CH * c - skew;  // row + ph at step 0 of the chunk
             int so = sig_off(ir0 + CH);
             int mo = mbase + (ir0 - ph) * mstep + pl;
-            T inz = lane_from(oz, srcZ);
 #pragma unroll
             for (int b = 0; b < CH; ++b, so += sstep, mo += mstep) {
                 T iny = lane_shr1(oy);
@@ -1265,19 +1306,21 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
             }
             // hand the outflow over and free the inflow before anything else
             done += step_;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            if (tells) __hip_atomic_store(tell, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __hip_atomic_store(tell, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            const T fwy = sF[w][2 + spy][e][ro], fwz = sF[w][2 + NS + spz][e][ro];
 #pragma unroll
             for (int b = 0; b < CH; ++b) *(T *)(qb[b] + b * RB) = po[b];
+            put_faces(CH, fwy, fwz);
             // psi rows 8c-16 .. 8c-9 (counted with the idle steps) are
             // complete, and go back
-            const int qw = q0 == RQ - CH ? 0 : q0 + CH;
-            put_rows(qw);
-            put_faces(CH, spy, spz);
+            q0 = q0 == RQ - CH ? 0 : q0 + CH;
+            get_rows(q0);
             slot += step_;
             slot = slot == NS ? 0 : slot;
-            q0 = qw;
             s0 = s0 + CH < RQ ? s0 + CH : s0 + CH - RQ;
+            enter(c + 1);
+            put_rows();
         }
     }
     if (!good) abort_all();
@@ -1388,8 +1431,8 @@ static const void *sweep_kernel_xcd(int wpb, int mode, bool sm, bool nt)
 bool sweep_xcd_supported(bool fp64, int mode, int wpb) { return !fp64 && mode == kFixup && wpb >= 1 && wpb <= 4; }
 
 // Tile variants: (teams, r) as the launch shape names them, and the waves of a
-// team.  A block holds w teams of 4 waves (r = 2), or for r = 4 one of 16 or
-// two of 8 in FP32 and one of 8 in FP64, whose rows take twice the LDS.
+// team.  A block holds w teams of 4 waves (r = 2) or of 8 (r = 4); FP64 rows
+// take twice the LDS, so its list stops at 8 waves.
 #define DSN_TILE_F32(X) X(1, 2) X(1, 4) X(2, 2) X(2, 4)
 #define DSN_TILE_F64(X) X(1, 2) X(1, 4)
 static int tile_team(bool fp64, int w, int r) { return r == 2 ? 4 : !fp64 && w == 1 ? 16 : 8; }
@@ -1587,7 +1630,7 @@ int sweep_grid_tile(int w, int r, int mode, int nx, int n_cu)
         const void *f = sweep_kernel_tile<T>(w, r, mode, sm != 0, false);
         if (!f) return 0;
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * tile_waves(ts == 8, w, r), 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * tile_waves(sizeof(T) == 8, w, r), 0) != hipSuccess ||
             n < 1) {
             (void)hipGetLastError();
             return 0;
