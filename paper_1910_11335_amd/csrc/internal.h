@@ -108,6 +108,9 @@ struct SolveArgs {
     // persistent sweep work queue
     int *sweep_ctr;           // the sweep counter block (sweep_counters_next)
     int *blk_done;            // [S]: blocks of the running moments pass that have written their partials
+    unsigned long long *prog; // [S]: pinned host words in which the moments pass reports each iteration
+                              // (prog_tag + group) << 32 | iterations << 1 | done, or null
+    unsigned prog_tag;        // tells this call's reports from earlier ones
     int *face_par;            // [S]: sign-bit parity of the next sweep's face words
     const int *sweep_dstart;  // [NJ+NK] first ticket of each pencil diagonal (+ total)
     int sweep_nitems;
@@ -162,6 +165,7 @@ __host__ __device__ inline SolveArgs<T> at_source(SolveArgs<T> a, int s)
         a.src_par += (long)kSrcPar * s;
         a.face_par += s;
         a.blk_done += s;
+        if (a.prog) a.prog += s;
         a.src_spec += (long)s * a.G;
     }
     return a;
@@ -172,6 +176,8 @@ __host__ __device__ inline SolveArgs<T> at_source(SolveArgs<T> a, int s)
 namespace dsn {
 
 // launchers (kernels.hip)
+void launch_put_sources(double *par, int npar, double *spec, int nspec, const double *host, hipStream_t s);
+void launch_report(const Ctl *ctl, int n, const int *ctr, Ctl *host_ctl, int *host_flags, hipStream_t s);
 void launch_voxels_to_pencils(const Geom &g, const uint8_t *mat_nat, const double *dens_nat, uint8_t *mat,
                               double *dens, hipStream_t s);
 template <typename T>

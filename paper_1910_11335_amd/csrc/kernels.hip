@@ -656,6 +656,36 @@ __device__ __forceinline__ void resid_body(Ctl *ctl, int g, const double *part, 
     ctl[g] = c;
 }
 
+// Source parameters and spectra out of pinned host memory.
+__global__ __launch_bounds__(256) void k_put_sources(double *par, int npar, double *spec, int nspec, const double *host)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < npar) par[i] = host[i];
+    else if (i < npar + nspec) spec[i - npar] = host[i];
+}
+
+void launch_put_sources(double *par, int npar, double *spec, int nspec, const double *host, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_put_sources, dim3((npar + nspec + 255) / 256), dim3(256), 0, s, par, npar, spec, nspec, host);
+}
+
+// The control blocks (n doubles) and the sweep's two flags into pinned host
+// memory.
+__global__ __launch_bounds__(256) void k_report(const double *ctl, int n, const int *ctr, double *host_ctl, int *host_flags)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) host_ctl[i] = ctl[i];
+    if (i < 2) host_flags[i] = ctr[i];
+}
+
+void launch_report(const Ctl *ctl, int n, const int *ctr, Ctl *host_ctl, int *host_flags, hipStream_t s)
+{
+    static_assert(sizeof(Ctl) % sizeof(double) == 0, "copied as doubles");
+    const int nd = n * (int)(sizeof(Ctl) / sizeof(double));
+    hipLaunchKernelGGL(k_report, dim3((nd + 255) / 256), dim3(256), 0, s, (const double *)ctl, nd, ctr,
+                       (double *)host_ctl, host_flags);
+}
+
 // EXPAND: also form the next iteration's directional source from the new
 // moments (the work of k_m2d, while the moments are still in registers), so
 // an iteration is one sweep and one pass over psi.
@@ -738,6 +768,12 @@ __device__ __forceinline__ void d2m_body(const SolveArgs<T> &a, int g, unsigned 
     if (threadIdx.x == 0) {
         *a.blk_done = 0;
         if (flip) *a.face_par ^= 1;
+        if (a.prog) {
+            const Ctl &c = a.ctl[g];
+            __hip_atomic_store(a.prog,
+                               (unsigned long long)(a.prog_tag + g) << 32 | (unsigned)c.iters << 1 | (c.done ? 1u : 0u),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
 }
 
