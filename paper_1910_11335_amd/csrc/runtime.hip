@@ -310,10 +310,11 @@ int tile_grid_of(const DeviceState &d, int w, int r)
 // time.  Tiles win where the chain of pencils bounds the sweep, pencils where
 // the memory does; what tells them apart is the number of rounds in which the
 // resident waves (16 a CU in FP32, 8 in FP64) sweep the pencil-directions.
-// Measured per sweep, pencil default against tile (us): 1.2 rounds (64^3 S8
-// FP32) 160 / 105, 5 rounds (128^3 S8 FP32) 439 / 368, 5.6 rounds (8 sources,
-// 48^3 S8 FP32) 209 / 207, 9 rounds (64^3 S16 FP64) 364 / 378, 18 rounds
-// (128^3 S16 FP32) 1083 / 1127.  The larger team saves hops through memory but
+// Measured per sweep, pencil default against tile (us), FP32: 1.2 rounds (64^3
+// S8) 160 / 105, 5 rounds (128^3 S8) 436 / 352, 10 rounds (96^3 S16) 510 / 494,
+// 18 rounds (128^3 S16) 1095 / 1093; a batch of 22 rounds on three streams 160.1 /
+// 159.2 ms.  FP64: 2.5 rounds (64^3 S8) 217 / 166, 9 rounds (64^3 S16) 370 / 365,
+// 20 rounds (96^3 S16) 990 / 1041.  The larger team saves hops through memory but
 // keeps a direction's waves on one CU: it wins where the waves fill the machine
 // about once anyway and the pencils are short (solves, team of 4 / larger, ms:
 // 40^3 S8 FP32 2.06 / 1.87, 48^3 S8 FP32 2.37 / 2.16, 20x100x30 S8 FP32 1.97 /
@@ -336,7 +337,7 @@ SweepShape default_shape(const dsn_problem *p, int S, int n_cu, double rounds_be
     };
     SweepShape x;
     const double rounds = sweep_rounds(p, S, n_cu) + rounds_beside;
-    if (pens > 1 && rounds < 8.0) {
+    if (pens > 1 && rounds < (fp64 ? 12.0 : 24.0)) {
         x.wpb = 1;
         x.relay = rounds >= 0.4 && rounds <= 1.25 && p->geom.nx <= 48 ? 4 : 2;
         x.blocks = tile_blocks(x.wpb, x.relay);
