@@ -498,17 +498,20 @@ dsn_status sweep_failed(dsn_problem *p, int flag)
     return fail(DSN_ERR_DEVICE, "sweep dependency wait timed out (results invalid)");
 }
 
+// Staging for n sources' parameters.  Until there is a larger block the handle
+// keeps the one it has.
 dsn_status ensure_source_staging(dsn_problem *p, int n)
 {
     DeviceState &d = p->dev;
     if (n <= d.h_src_cap) return DSN_OK;
-    if (d.h_src_own) (void)hipHostFree(d.h_src_own);
-    d.h_src = d.h_src_own = nullptr;
-    d.h_src_cap = 0;
-    if (hipHostMalloc((void **)&d.h_src_own, (size_t)n * (kSrcPar + p->G) * sizeof(double),
-                      hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess)
+    double *q = nullptr;
+    if (hipHostMalloc((void **)&q, (size_t)n * (kSrcPar + p->G) * sizeof(double),
+                      hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess) {
+        (void)hipGetLastError();
         return fail(DSN_ERR_OUT_OF_MEMORY, "hipHostMalloc failed");
-    d.h_src = d.h_src_own;
+    }
+    if (d.h_src_own) (void)hipHostFree(d.h_src_own);
+    d.h_src = d.h_src_own = q;
     d.h_src_cap = n;
     return DSN_OK;
 }
