@@ -169,7 +169,9 @@ typedef struct {
                                    counts are the same.
                                    dsn_solve_batch rejects 1; the adjoint
                                    ignores it. */
-    void *stream;               /* hipStream_t to run on, NULL = null stream     */
+    void *stream;               /* hipStream_t to run on, NULL = null stream.
+                                   Solves wait for it: one that is being
+                                   captured is refused (DSN_ERR_DEVICE)          */
     int32_t stop_rule;          /* 0 or 1, see above                             */
     int32_t batch_mode;         /* 0 or 1 (every call checks it; only
                                    dsn_solve_batch uses it):

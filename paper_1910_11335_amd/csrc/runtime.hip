@@ -498,6 +498,17 @@ dsn_status sweep_failed(dsn_problem *p, int flag)
     return fail(DSN_ERR_DEVICE, "sweep dependency wait timed out (results invalid)");
 }
 
+// Solves wait for their stream, so they cannot run on one that is being
+// captured.  Refused before anything is recorded there: the handle would count
+// on fills and sweeps that only a replay carries out.
+dsn_status refuse_capture(hipStream_t s)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    DSN_HIP(hipStreamIsCapturing(s, &c));
+    if (c != hipStreamCaptureStatusNone) return fail(DSN_ERR_DEVICE, "the stream is being captured");
+    return DSN_OK;
+}
+
 // Staging for n sources' parameters.  Until there is a larger block the handle
 // keeps the one it has.
 dsn_status ensure_source_staging(dsn_problem *p, int n)
@@ -1096,8 +1107,7 @@ dsn_status iterate_group(dsn_problem *p, SolveArgs<T> &a, int g, const dsn_solve
             DSN_HIP(hipGetLastError());
             looks = 0;
         } else if (looks % 4096 == 0) {
-            // still running?  (Fails also on a stream that is being captured,
-            // where nothing runs.)
+            // still running?
             const hipError_t e = hipStreamQuery(s);
             if (e == hipErrorNotReady) (void)hipGetLastError();
             else DSN_HIP(e);
@@ -2265,6 +2275,7 @@ dsn_status dsn_solve(dsn_problem *p, const dsn_source *src, int32_t n_src, const
         if (n_src == 0) return DSN_OK;
         if ((st = ensure_device(p)) != DSN_OK) return st;
         hipStream_t s = (hipStream_t)opts->stream;
+        if ((st = refuse_capture(s)) != DSN_OK) return st;
         p->dev.rounds_beside = 0.0;
         StageTimer &tm = p->dev.timer;
         tm.on = opts->profile != 0;
@@ -2340,8 +2351,9 @@ dsn_status dsn_solve_adjoint(dsn_problem *p, const dsn_source *src, const double
         if (st != DSN_OK) return st;
         if ((st = check_source(p, *src)) != DSN_OK) return st;
         if ((st = ensure_device(p)) != DSN_OK) return st;
-        if ((st = ensure_adjoint(p)) != DSN_OK) return st;
         hipStream_t s = (hipStream_t)opts->stream;
+        if ((st = refuse_capture(s)) != DSN_OK) return st;
+        if ((st = ensure_adjoint(p)) != DSN_OK) return st;
         p->dev.rounds_beside = 0.0;
         p->dev.timer.on = false;
         if (info) {
@@ -2458,6 +2470,10 @@ dsn_status dsn_solve_batch(dsn_problem *const *probs, int32_t n_probs, const dsn
             info->sweep_xcd_queues = 0;
             info->sweep_relay = 0;
             for (int k = 0; k < DSN_NUM_STAGES; ++k) { info->stage_ms[k] = 0; info->stage_launches[k] = 0; }
+        }
+        {
+            const dsn_status st = refuse_capture((hipStream_t)opts->stream);
+            if (st != DSN_OK) return st;
         }
         // fused: one sweep launch per iteration over every (problem, source) pair
         if (opts->batch_mode == 1) {

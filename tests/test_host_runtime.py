@@ -18,3 +18,44 @@ fake.fake_host_limit(1 << 40)
 assert solve(h, n_src=200, combine=True)[0] == dsn.DSN_OK, dsn.last_error()
 h.close()
 ''')
+
+
+def test_capturing_stream_is_refused_untouched():
+    """A solve on a stream that is being captured is refused before anything
+    is recorded, and the handle's later solves still clear the face words of
+    the sweep before when its shape has changed: here the single-pencil words
+    and then a tile's."""
+    fake_hip.run('''
+stream = 0x1000
+for entry in ("solve", "adjoint", "batch", "fused"):
+    h = problem((9, 20, 18), 4, G=2, fixup=1)
+    h.set_sweep_shape(1, 16)
+    assert solve(h, stream=stream)[0] == dsn.DSN_OK
+    h.set_sweep_shape(1, 16, 0, 2)
+    events()
+    fake.fake_capture(stream, 1)
+    src = SourceSpec(position=(-2.3, 0.7, 0.9), spectrum=np.ones(2))
+    s, keep = dsn._source_struct(src, 2)
+    o, keep2 = dsn._opts(2, 1e-5, 100, [2, 2], False, stream, batch_mode=int(entry == "fused"))
+    buf = np.zeros(8)
+    ptr = buf.ctypes.data_as(C.c_void_p)
+    if entry == "solve":
+        st = solve(h, stream=stream)[0]
+        assert solve(h, stream=stream, iters=None)[0] == dsn.DSN_ERR_DEVICE
+    elif entry == "adjoint":
+        J = C.c_double()
+        st = dsn.lib().dsn_solve_adjoint(h.handle, C.byref(s), ptr, C.byref(o), C.byref(J), ptr, None, None)
+    else:
+        st = dsn.lib().dsn_solve_batch((C.c_void_p * 1)(h.handle.value), 1, (C.POINTER(dsn.Source) * 1)(C.pointer(s)),
+                                       np.ones(1, np.int32).ctypes.data_as(dsn._ip), C.byref(o),
+                                       (C.c_void_p * 1)(buf.ctypes.data), None)
+    assert st == dsn.DSN_ERR_DEVICE, (entry, st)
+    log = events()
+    assert not [e for e in log if "captured" in e], (entry, log)
+    fake.fake_capture(stream, 0)
+    assert solve(h, stream=stream)[0] == dsn.DSN_OK
+    log = events()
+    sweep = min(i for i, e in enumerate(log) if "k_sweep_tile" in e)
+    assert "fill" in log[:sweep], (entry, log)
+    h.close()
+''')
