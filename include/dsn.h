@@ -350,8 +350,11 @@ dsn_status dsn_dose(dsn_problem *p, const double *phi, int32_t n, const double *
  *     directions of an octant, xcd_queues be 0, and waves_per_block x R
  *     pencils of the x extent fit a compute unit's LDS (nx up to 970 for
  *     (1, 4) in FP32, 357 in FP64).  The tile's rectangle follows from the
- *     mesh.  The default shape of an untuned handle is one of these where
- *     the pencils' dependency chain bounds the sweep.
+ *     mesh.  A mesh whose row of (ny / 8 + 1) pencil faces along y takes more
+ *     than 2 GiB (64 bytes a row of 8 voxels in FP32, 128 in FP64) is swept by
+ *     pencil items of waves_per_block directions instead.  The default shape
+ *     of an untuned handle is one of these where the pencils' dependency
+ *     chain bounds the sweep.
  * blocks per launch: 1..2^20 (the sweep's persistent blocks take work from a
  * ticket queue, so any count is correct and about the resident count is
  * fastest).  Every shape gives the same results bit for bit.  The handle

@@ -196,8 +196,9 @@ template <typename T>
 int sweep_grid(int wpb, int mode, int n_cu);
 int sweep_tile_choices(bool fp64, int *w_out, int *r_out);  // (teams, r) of the built tile sweeps
 void sweep_tile(bool fp64, int w, int r, int NJ, int NK, int *ty, int *tz);  // the tile of a team, in pencils
+bool sweep_tile_addressable(bool fp64, int nx, int NJ);  // the tile sweep's face offsets cover such a mesh
 template <typename T>
-int sweep_grid_tile(int w, int r, int mode, int nx, int n_cu);
+int sweep_grid_tile(int w, int r, int mode, int nx, int NJ, int n_cu);
 // follow: launch_d2m with the same arguments comes next on the stream;
 // ev_before / ev_after (may be null): recorded on s right around the sweep
 // kernel itself

@@ -332,8 +332,8 @@ SweepShape default_shape(const dsn_problem *p, int S, int n_cu, double rounds_be
     const bool fp64 = p->precision == DSN_FP64;
     const int NJ = p->geom.NJ, NK = p->geom.NK, pens = NJ * NK;
     auto tile_blocks = [&](int w, int r) {
-        return fp64 ? sweep_grid_tile<double>(w, r, p->fixup, p->geom.nx, n_cu)
-                    : sweep_grid_tile<float>(w, r, p->fixup, p->geom.nx, n_cu);
+        return fp64 ? sweep_grid_tile<double>(w, r, p->fixup, p->geom.nx, NJ, n_cu)
+                    : sweep_grid_tile<float>(w, r, p->fixup, p->geom.nx, NJ, n_cu);
     };
     SweepShape x;
     const double rounds = sweep_rounds(p, S, n_cu) + rounds_beside;
@@ -708,8 +708,8 @@ dsn_status ensure_device(dsn_problem *p)
             d.tile_w[d.ntile] = tw[i];
             d.tile_r[d.ntile] = tr[i];
             d.tile_grid[d.ntile++] =
-                f32 ? sweep_grid_tile<float>(tw[i], tr[i], p->fixup, p->geom.nx, prop.multiProcessorCount)
-                    : sweep_grid_tile<double>(tw[i], tr[i], p->fixup, p->geom.nx, prop.multiProcessorCount);
+                f32 ? sweep_grid_tile<float>(tw[i], tr[i], p->fixup, p->geom.nx, p->geom.NJ, prop.multiProcessorCount)
+                    : sweep_grid_tile<double>(tw[i], tr[i], p->fixup, p->geom.nx, p->geom.NJ, prop.multiProcessorCount);
         }
     }
     if (e != hipSuccess) {
@@ -2083,6 +2083,7 @@ dsn_status dsn_set_sweep_shape(dsn_problem *p, int32_t waves_per_block, int32_t 
         if (st != DSN_OK) return st;
         DeviceState &d = p->dev;
         if (d.grid_of[w] < 1) return fail(DSN_ERR_UNSUPPORTED, "no sweep kernel of that shape fits the device");
+        if (relay > 0 && !sweep_tile_addressable(fp64, p->geom.nx, p->geom.NJ)) relay = 0;
         if (relay > 0 && tile_grid_of(d, w, relay) < 1)
             return fail(DSN_ERR_UNSUPPORTED, "the tile shape is not built for this x extent");
         if (xcd_queues != 0) {

@@ -1635,14 +1635,24 @@ int launch_sweep_multi(const SolveArgs<T> &a, const SolveArgs<T> *host_tab, int 
     return 1;
 }
 
+// A tile wave's z faces, the upstream pencil's and its own, lie in one buffer
+// of a row of NJ + 1 pencil faces, with offsets from kNone = 2^31 up outside
+// it.  (In FP64 a row that long belongs to a mesh of 100 GB and more.)
+bool sweep_tile_addressable(bool fp64, int nx, int NJ)
+{
+    const long face_row = 8L * (fp64 ? TaggedFace<double>::BYTES : TaggedFace<float>::BYTES);  // the widest codec
+    return (NJ + 1L) * nx * face_row <= 1L << 31;
+}
+
 // Resident blocks of the tile sweep of shape (w, r) in cell mode `mode` (grid
-// size), 0 if there is no such kernel, or for an x extent beyond the shapes'
-// range: w * r pencils of an x extent must fit a CU's LDS (nx up to 970 for
+// size), 0 if there is no such kernel, for a mesh beyond its face offsets or
+// for an x extent beyond the shapes' range: w * r pencils of an x extent must fit a CU's LDS (nx up to 970 for
 // (1, 4) in FP32, 357 in FP64), the range pinned shapes have been accepted for.
 template <typename T>
-int sweep_grid_tile(int w, int r, int mode, int nx, int n_cu)
+int sweep_grid_tile(int w, int r, int mode, int nx, int NJ, int n_cu)
 {
     const long ts = sizeof(T);
+    if (!sweep_tile_addressable(sizeof(T) == 8, nx, NJ)) return 0;
     if (w * r * (24 * 64 * ts + 4 * 16 * 8 * ts + 24 * 64 + nx * 8L * ts) + 256 > 160 * 1024) return 0;
     int per_cu = 1 << 30;
     for (int sm = 0; sm < 2; ++sm) {
@@ -1733,8 +1743,8 @@ void launch_checksum(const void *x, long n_words, unsigned long long *out, hipSt
 
 template int sweep_grid<float>(int, int, int);
 template int sweep_grid<double>(int, int, int);
-template int sweep_grid_tile<float>(int, int, int, int, int);
-template int sweep_grid_tile<double>(int, int, int, int, int);
+template int sweep_grid_tile<float>(int, int, int, int, int, int);
+template int sweep_grid_tile<double>(int, int, int, int, int, int);
 template int launch_sweeps<float>(const SolveArgs<float> &, int, hipStream_t, bool, hipEvent_t, hipEvent_t);
 template int launch_sweeps<double>(const SolveArgs<double> &, int, hipStream_t, bool, hipEvent_t, hipEvent_t);
 template bool sweep_flips_parity<float>(const SolveArgs<float> &);

@@ -59,3 +59,26 @@ for entry in ("solve", "adjoint", "batch", "fused"):
     assert "fill" in log[:sweep], (entry, log)
     h.close()
 ''')
+
+
+def test_tile_shape_beyond_its_face_offsets_runs_as_pencils():
+    """A tile's z faces are addressed with 32-bit offsets over a row of
+    pencils, of which the upper half means no face.  In FP64 a row of 32767
+    pencils of 512 voxels just fits; one pencil more, and a handle pinned to
+    a tile shape sweeps by pencils of as many directions."""
+    fake_hip.run('''
+from types import SimpleNamespace
+def kernels(NJ):
+    n = (512, 8 * NJ, 1)
+    h = dsn.Problem(SimpleNamespace(nx=n[0], ny=n[1], nz=n[2], dx=1.0, dy=1.0, dz=1.0, density=None, fixup=0,
+                    material=np.zeros(n[0] * n[1], np.uint8), sigma_t=np.ones((1, 1)), sigma_s=np.zeros((1, 1, 1, 1)),
+                    sn_order=2, legendre_order=0), "fp64")
+    h.set_sweep_shape(1, 64, 0, 2)
+    events()
+    st, info = solve(h)
+    assert st == dsn.DSN_OK, dsn.last_error()
+    h.close()
+    return info.sweep_relay, ["k_sweep_tile" in e for e in events() if "k_sweep" in e]
+assert kernels(32767) == (2, [True, True])
+assert kernels(32768) == (0, [False, False])
+''')
