@@ -306,45 +306,75 @@ int tile_grid_of(const DeviceState &d, int w, int r)
     return 0;
 }
 
+// Waves that sweep one direction in tile shape (1, relay), those of a tile
+// that lie outside the mesh included.
+int tile_waves_of_direction(const dsn_problem *p, int relay)
+{
+    int ty = 1, tz = 1;
+    sweep_tile(p->precision == DSN_FP64, 1, relay, p->geom.NJ, p->geom.NK, &ty, &tz);
+    return (p->geom.NJ + ty - 1) / ty * ty * ((p->geom.NK + tz - 1) / tz * tz);
+}
+// Rounds of the machine that so many waves a direction take, for S sources, in
+// units of 16 waves a CU (FP32) or 8 (FP64).
+double sweep_rounds(const dsn_problem *p, int waves, int S, int n_cu)
+{
+    return S * (double)p->Nd * waves / (n_cu * (p->precision == DSN_FP64 ? 8.0 : 16.0));
+}
+
 // The launch shape of a handle that has not been tuned, for S sources at a
-// time.  Tiles win where the chain of pencils bounds the sweep, pencils where
-// the memory does; what tells them apart is the number of rounds in which the
-// resident waves (16 a CU in FP32, 8 in FP64) sweep the pencil-directions.
-// Measured per sweep, pencil default against tile (us), FP32: 1.2 rounds (64^3
-// S8) 160 / 105, 5 rounds (128^3 S8) 436 / 352, 10 rounds (96^3 S16) 510 / 494,
-// 18 rounds (128^3 S16) 1095 / 1093; a batch of 22 rounds on three streams 160.1 /
-// 159.2 ms.  FP64: 2.5 rounds (64^3 S8) 217 / 166, 9 rounds (64^3 S16) 370 / 365,
-// 20 rounds (96^3 S16) 990 / 1041.  The larger team saves hops through memory but
-// keeps a direction's waves on one CU: it wins where the waves fill the machine
-// about once anyway and the pencils are short (solves, team of 4 / larger, ms:
-// 40^3 S8 FP32 2.06 / 1.87, 48^3 S8 FP32 2.37 / 2.16, 20x100x30 S8 FP32 1.97 /
-// 1.73, 40^3 S8 FP64 4.23 / 4.05), not below (64x64x16 S6 FP32 81.8 / 86.7),
-// beyond (48^3 S8 FP64 5.09 / 5.65) or on long ones (100x20x30 S8 FP32 1.39 /
-// 1.56).
+// time.
+//
+// Teams of four against pencil items: tiles save time at every hop of the
+// chain of pencils along a diagonal, and lose some in every round of the
+// machine, where fewer and partly idle waves sweep the rows.  The line is where
+// the two are equal, with what they cost fitted to 2400 meshes (1 to 18 pencils
+// a side, nx 4 to 200, S2 to S16, 1 to 64 sources, 0.02 to 40 rounds), 20
+// iterations of a solve each: a hop saves 3.5 us in FP32 and 5.2 in FP64; a round
+// costs chunk_us more per 8-step chunk of a pencil and start_us less per
+// item, which depends on how many directions share a pencil item (its waves).
+// On these and 1200 more the pick is 1.26 times as fast as pencils alone, where
+// the best shape of each would be 1.27; it is slower than pencils by 5 % in 8 of
+// them and by 8 % at worst.
+// Pencils / tiles, ms a solve: 24x72x72 S8 FP32 4.08 / 2.80, 24x48x48 S8 FP64
+// 3.36 / 2.40, 24x24x24 S16 FP32 4 sources 2.25 / 2.61, 24x8x16 S16 FP32 40
+// sources 3.45 / 5.60, 24x24x24 S8 FP64 12 sources 3.45 / 4.30.
+//
+// The larger team saves hops through memory but keeps a direction's waves on
+// one CU: it wins where the waves fill the machine about once, the pencils are
+// short and not most of its waves idle (solves, team of 4 / larger, ms: 40^3 S8
+// FP32 2.06 / 1.87, 20x100x30 S8 FP32 1.97 / 1.73, 40^3 S8 FP64 4.23 / 4.05; but
+// 64x64x16 S6 FP32 81.8 / 86.7, 48^3 S8 FP64 5.09 / 5.65, 100x20x30 S8 FP32 1.39 /
+// 1.56, and with 11 of 16 waves idle, 24x8x40 S8 FP32 12 sources, 2.24 where
+// pencils take 1.94).
+//
 // Problems of a batch that sweep beside this one (on other streams) fill the
 // machine too: rounds_beside counts theirs.
-double sweep_rounds(const dsn_problem *p, int S, int n_cu)
-{
-    return (double)S * p->Nd * p->geom.NJ * p->geom.NK / ((double)n_cu * (p->precision == DSN_FP64 ? 8 : 16));
-}
 SweepShape default_shape(const dsn_problem *p, int S, int n_cu, double rounds_beside)
 {
-    const bool fp64 = p->precision == DSN_FP64;
-    const int NJ = p->geom.NJ, NK = p->geom.NK, pens = NJ * NK;
-    auto tile_blocks = [&](int w, int r) {
-        return fp64 ? sweep_grid_tile<double>(w, r, p->fixup, p->geom.nx, NJ, n_cu)
-                    : sweep_grid_tile<float>(w, r, p->fixup, p->geom.nx, NJ, n_cu);
-    };
+    const bool fp64 = p->precision == DSN_FP64, fixup = p->fixup != 0;
+    const int NJ = p->geom.NJ, NK = p->geom.NK, nx = p->geom.nx;
+    auto rounds = [&](int waves) { return sweep_rounds(p, waves, S, n_cu) + rounds_beside; };
     SweepShape x;
-    const double rounds = sweep_rounds(p, S, n_cu) + rounds_beside;
-    if (pens > 1 && rounds < (fp64 ? 12.0 : 24.0)) {
-        x.wpb = 1;
-        x.relay = rounds >= 0.4 && rounds <= 1.25 && p->geom.nx <= 48 ? 4 : 2;
-        x.blocks = tile_blocks(x.wpb, x.relay);
-        if (x.blocks > 0) return x;
-    }
-    x.relay = 0;
     x.wpb = sweep_wpb(p->D, fp64);
+    const double hop_us = fp64 ? 5.2 : 3.5;
+    const double chunk_us = fp64 ? (fixup ? 1.1 : 0.25) : (fixup ? 0.8 : 0.13);
+    const double start_us = fp64 ? (x.wpb == 1 ? 3.8 : -2.5) : x.wpb == 1 ? 8.0 : x.wpb == 2 ? 1.2 : -5.0;
+    const int chunks = (nx + 15) / 8 + 1, hops = NJ + NK - 2;
+    const double beyond = std::max(0.0, rounds(tile_waves_of_direction(p, 2)) - 0.4);  // (the first is no loss)
+    if (hops > 0 && hops * hop_us > beyond * (chunks * chunk_us - start_us)) {
+        const int large = tile_waves_of_direction(p, 4);
+        const double once = rounds(NJ * NK);
+        const int relay =
+            once >= 0.4 && once <= 1.25 && nx <= 48 && large <= 2.6 * NJ * NK && rounds(large) <= 2.0 ? 4 : 2;
+        const int blocks = fp64 ? sweep_grid_tile<double>(1, relay, p->fixup, nx, NJ, n_cu)
+                                : sweep_grid_tile<float>(1, relay, p->fixup, nx, NJ, n_cu);
+        if (blocks > 0) {
+            x.wpb = 1;
+            x.relay = relay;
+            x.blocks = blocks;
+            return x;
+        }
+    }
     x.blocks = fp64 ? sweep_grid<double>(x.wpb, p->fixup, n_cu) : sweep_grid<float>(x.wpb, p->fixup, n_cu);
     return x;
 }
@@ -2511,12 +2541,23 @@ dsn_status dsn_solve_batch(dsn_problem *const *probs, int32_t n_probs, const dsn
             const dsn_status st = joint_batch_limits(probs, n_probs, n_src, per_batch);
             if (st != DSN_OK) return st;
         }
+        // Of the other problems' sweeps about one and a half run beside a
+        // problem's own: the streams share four hardware queues, with moments
+        // passes and launch gaps between the sweeps (160 batches of 2 to 40
+        // phantoms: the shapes so picked are within 0.4 % of the better of all
+        // tiles and all pencils on average; with every sweep counted, 2.7 %).
         double rounds = 0.0;
-        for (int b = 0; b < n_probs; ++b)
-            if (n_src[b] > 0) rounds += sweep_rounds(probs[b], per_batch[b], probs[b]->dev.n_cu);
+        int active = 0;
+        std::vector<double> own(n_probs, 0.0);
+        for (int b = 0; b < n_probs; ++b) {
+            if (n_src[b] == 0) continue;
+            rounds += own[b] =
+                sweep_rounds(probs[b], tile_waves_of_direction(probs[b], 2), per_batch[b], probs[b]->dev.n_cu);
+            ++active;
+        }
         for (int b = 0; b < n_probs; ++b)
             if (n_src[b] > 0)
-                probs[b]->dev.rounds_beside = rounds - sweep_rounds(probs[b], per_batch[b], probs[b]->dev.n_cu);
+                probs[b]->dev.rounds_beside = (rounds - own[b]) * std::min(1.0, 1.5 / std::max(1, active - 1));
         std::vector<Job> jobs(n_probs);
         std::vector<std::thread> workers;
         struct JoinAll {  // joins the started workers on every way out, exceptions included

@@ -82,3 +82,38 @@ def kernels(NJ):
 assert kernels(32767) == (2, [True, True])
 assert kernels(32768) == (0, [False, False])
 ''')
+
+
+# default shapes by mesh, order, precision, fixup and sources, where one kind
+# of item was measured at least a tenth faster: time of a solve on pencils over
+# that on tiles
+FASTER_ON = [
+    ("pencils", (24, 8, 16), 16, "fp32", 1, 40, 0.62),
+    ("pencils", (24, 24, 24), 16, "fp32", 1, 12, 0.74),
+    ("pencils", (24, 40, 40), 16, "fp32", 1, 4, 0.77),
+    ("pencils", (64, 24, 24), 8, "fp32", 1, 40, 0.85),
+    ("pencils", (24, 24, 24), 16, "fp64", 1, 4, 0.80),
+    ("pencils", (24, 8, 16), 8, "fp64", 1, 40, 0.73),
+    ("pencils", (24, 8, 40), 8, "fp64", 0, 40, 0.85),
+    ("pencils", (24, 8, 8), 10, "fp32", 0, 64, 0.0),  # a single pencil: nothing to hand over
+    ("tiles", (24, 72, 72), 8, "fp32", 1, 1, 1.46),
+    ("tiles", (8, 24, 24), 8, "fp32", 1, 40, 1.26),
+    ("tiles", (24, 32, 32), 8, "fp32", 0, 40, 1.31),
+    ("tiles", (24, 48, 48), 16, "fp32", 1, 1, 1.21),
+    ("tiles", (64, 64, 64), 8, "fp32", 1, 1, 1.45),
+    ("tiles", (24, 48, 48), 8, "fp64", 1, 1, 1.40),
+    ("tiles", (24, 72, 72), 8, "fp64", 0, 1, 1.35),
+]
+
+
+def test_default_shape_is_the_faster_kind():
+    out = fake_hip.run('''
+for kind, n, sn, precision, fixup, n_src, gain in %r:
+    h = problem(n, sn, precision, fixup=fixup)
+    st, info = solve(h, n_src=n_src)
+    assert st == dsn.DSN_OK, dsn.last_error()
+    if ("tiles" if info.sweep_relay else "pencils") != kind:
+        print(kind, n, sn, precision, fixup, n_src, gain)
+    h.close()
+''' % (FASTER_ON,))
+    assert out == "", out
