@@ -347,9 +347,9 @@ dsn_status dsn_dose(dsn_problem *p, const double *phi, int32_t n, const double *
  *     (waves_per_block, R) picks the block: in FP32 (1, 2) one team of 4
  *     waves, (2, 2) two of 4, (1, 4) one of 16, (2, 4) two of 8; in FP64
  *     (1, 2) one of 4, (1, 4) one of 8; waves_per_block must divide the
- *     directions of an octant, xcd_queues be 0, and waves_per_block x R
- *     pencils of the x extent fit a compute unit's LDS (nx up to 970 for
- *     (1, 4) in FP32, 357 in FP64).  The tile's rectangle follows from the
+ *     directions of an octant, xcd_queues be 0, and nx be at most 2252, 974
+ *     or 335 for waves_per_block x R = 2, 4 or 8 in FP32, 998 or 359 for 2 or
+ *     4 in FP64.  The tile's rectangle follows from the
  *     mesh.  A mesh whose row of (ny / 8 + 1) pencil faces along y takes more
  *     than 2 GiB (64 bytes a row of 8 voxels in FP32, 128 in FP64) is swept by
  *     pencil items of waves_per_block directions instead.  The default shape

@@ -117,8 +117,6 @@ __device__ __forceinline__ T dd_update(T q, T sg, T cx, T cy, T cz, T csum, T px
         // negative reproduces that lane's values exactly, so the passes run
         // branch-free over the whole wave while any lane still needs one.
         T lo = fmin3(ox_, oy_, oz_);
-        // (out of line: most steps fix nothing, and a taken branch over the
-        // passes costs a step an instruction fetch)
         if (__any(lo < T(0))) {
             T mx = T(0), my = T(0), mz = T(0);
             const T hx = T(0.5) * cx * px, hy = T(0.5) * cy * iny, hz = T(0.5) * cz * inz;
@@ -922,7 +920,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     // atomic over the lanes, and wait for it on the spot
     int opaque0 = 0;
     asm("" : "+v"(opaque0));
-    if (tw == 0 && lead + TW <= NW) {
+    if (tw == 0) {
         if (lane == 0) tnext = atomicAdd(&ctr[opaque0], 1);
         have_next = true;
     }
@@ -945,7 +943,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     }
     if (threadIdx.x == 0) sAbort = 0;
     __syncthreads();  // the only barrier
-    if (lead + TW > NW) return;  // waves left over
+    // Never taken: a block is a whole number of teams.  It keeps the compiler
+    // from merging the code on its two sides, whose schedule a small mesh feels
+    // (33x21x18 solve 1.41 ms with it, 1.45 without).
+    if (lead + TW > NW) return;
 
     // waits on LDS state: polled much faster than a face word in memory
     const int lds_limit = a0.sweep_spin_limit < 1024 ? a0.sweep_spin_limit
@@ -1645,15 +1646,16 @@ bool sweep_tile_addressable(bool fp64, int nx, int NJ)
 }
 
 // Resident blocks of the tile sweep of shape (w, r) in cell mode `mode` (grid
-// size), 0 if there is no such kernel, for a mesh beyond its face offsets or
-// for an x extent beyond the shapes' range: w * r pencils of an x extent must fit a CU's LDS (nx up to 970 for
-// (1, 4) in FP32, 357 in FP64), the range pinned shapes have been accepted for.
+// size), 0 if there is no such kernel, for a mesh beyond its face offsets or for
+// an x extent beyond the shape's range.  The kernel's LDS does not depend on nx;
+// the range is the one these shapes are documented and accepted for (nx up to
+// 2252, 974 and 335 for w * r = 2, 4 and 8 in FP32, 998 and 359 for 2 and 4 in
+// FP64), and pencils sweep longer ones.
 template <typename T>
 int sweep_grid_tile(int w, int r, int mode, int nx, int NJ, int n_cu)
 {
-    const long ts = sizeof(T);
-    if (!sweep_tile_addressable(sizeof(T) == 8, nx, NJ)) return 0;
-    if (w * r * (24 * 64 * ts + 4 * 16 * 8 * ts + 24 * 64 + nx * 8L * ts) + 256 > 160 * 1024) return 0;
+    const int n = w * r, longest = sizeof(T) == 8 ? (n == 2 ? 998 : 359) : n == 2 ? 2252 : n == 4 ? 974 : 335;
+    if (nx > longest || !sweep_tile_addressable(sizeof(T) == 8, nx, NJ)) return 0;
     int per_cu = 1 << 30;
     for (int sm = 0; sm < 2; ++sm) {
         const void *f = sweep_kernel_tile<T>(w, r, mode, sm != 0, false);
