@@ -30,21 +30,31 @@ TRAFFIC_SUMMARY = {"k_sweep": (os.path.join(ROOT, "profiles", "k_sweep_cfg3_fp32
                    "k_d2m": (os.path.join(ROOT, "profiles", "k_d2m_cfg3_fp32.md"), os.path.join(CSRC, "kernels.hip"))}
 
 
-def measured_traffic(kernel, workload, precision):
+def measured_traffic(kernel, workload, precision, key=None):
     """HBM bytes per launch of `kernel` from its committed rocprofv3 counter
     summary (FETCH_SIZE + WRITE_SIZE, copy-calibrated), or None when that
     summary does not cover this workload or the kernel source has changed
-    since the counters were taken."""
+    since the counters were taken.  key: the launch shape as sweep_kernel()
+    names it, whose own figure is taken (None if the summary has none)."""
     import re
     summary, source = TRAFFIC_SUMMARY[kernel]
     if workload != "cfg3" or precision != "fp32" or not os.path.exists(summary):
         return None
     text = open(summary).read()
-    t = re.search(r"traffic_bytes_per_launch: ([0-9.eE+]+)", text)
+    t = re.search(r"traffic_bytes_per_launch%s: ([0-9.eE+]+)" % re.escape("[%s]" % key if key else ""), text)
     h = re.search(r"kernel_source_sha256_prefix: ([0-9a-f]+)", text)
     if not t or not h:
         return None
     return float(t.group(1)) if kernel_source_digest(source).startswith(h.group(1)) else None
+
+
+def sweep_kernel(shape):
+    """The kernel that sweeps in a launch shape (waves per block, blocks,
+    per-XCD queues, R), and the shape's name in the counter summary."""
+    w, _, xcd, relay = shape
+    if relay:
+        return "k_sweep_tile", "tile %dx%d" % (w, relay)
+    return "k_sweep", "%s %d" % ("xcd" if xcd else "pencils", w)
 
 
 def kernel_source_digest(path):
@@ -466,7 +476,8 @@ def main():
     torch.cuda.synchronize()
     dt_plain = time.perf_counter() - t1
     sweep_s = stage_ms["sweep"] / 1e3
-    traffic = measured_traffic("k_sweep", args.workload, args.precision)
+    sweep_name, sweep_key = sweep_kernel(tuned["sweep_shape"])
+    traffic = measured_traffic("k_sweep", args.workload, args.precision, sweep_key)
     achieved = sweep_bytes / sweep_s / 1e9 if sweep_s > 0 else 0.0
     # k_d2m (moments, residual partials and the next directional source),
     # with its last block's convergence test
@@ -503,7 +514,7 @@ def main():
                             "xcd_queues": tuned["sweep_shape"][2], "relay": tuned["sweep_shape"][3],
                             "timed_ms": {"%dx%d%s" % (w, b, "/xcd" if x else "/relay%d" % r if r else ""): round(ms, 4)
                                          for w, b, x, r, ms in h.sweep_tuning()}}},
-        "roofline": {"kernel": "k_sweep", "bound": "hbm", "achieved": achieved, "peak": MI355X_HBM_PEAK_GBS,
+        "roofline": {"kernel": sweep_name, "bound": "hbm", "achieved": achieved, "peak": MI355X_HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / MI355X_HBM_PEAK_GBS,
                      "traffic": traffic / 1e9 if traffic else None, "traffic_unit": "GB per launch (HBM)",
                      "algorithmic_GB_per_launch": sweep_bytes / max(1, launches["sweep"]) / 1e9,
