@@ -870,7 +870,7 @@ __device__ __forceinline__ void fetch_args()
 // every LDS trip of a chunk counts.  Hence one LDS trip between the steps of
 // two chunks, no branch off the common path, and addresses as immediate
 // offsets (64x64x16 S6 G90 solve 87.5 -> 81.9 ms, 40^3 S8 2.00 -> 1.87 ms).  The
-// sweep of 64^3 S8 takes 105 us (k_sweep: 146-160), in FP64 166 (202-217).
+// sweep of 64^3 S8 takes 92 us (k_sweep: 146-160), in FP64 144 (202-217).
 //
 // Global rim words: word (slot, entry) of a pencil face, slot = u mod nx with
 // u = row + the entry's skew along the face: a bijection of the nx rows of
