@@ -243,8 +243,8 @@ size_t dsn_workspace_bytes(const dsn_problem *p);
 dsn_status dsn_solve(dsn_problem *p, const dsn_source *src, int32_t n_src, const dsn_solve_opts *opts,
                      double *phi_total, double *phi_uncollided, dsn_solve_info *info);
 
-/* For callers that cannot allocate device memory (code under HIP graph
- * capture, tight serving loops, harnesses that forbid hipMalloc): the forward
+/* For callers that cannot allocate device memory (while another stream is
+ * captured, tight serving loops, harnesses that forbid hipMalloc): the forward
  * solve of dsn_solve for one source, computed by the same kernels in the
  * same order (identical results for the same sweep launch shape), that calls
  * no device allocation routine.  Every device array of the solve (problem

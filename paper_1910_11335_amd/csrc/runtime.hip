@@ -1948,6 +1948,7 @@ dsn_status solve_noalloc(dsn_problem *p, const dsn_source &src, const dsn_solve_
         return fail(DSN_ERR_UNSUPPORTED, "too many sweep items (directions x pencils)");
     dsn_status st = scratch_of(&base, &n_cu);
     if (st != DSN_OK) return st;
+    if ((st = refuse_capture(s)) != DSN_OK) return st;
     const SweepShape shape = own ? SweepShape{d.wpb, d.sweep_grid, 0, 0.f, d.relay} : default_shape(p, 1, n_cu, 0.0);
     const int wpb = shape.wpb, grid = shape.blocks, relay = shape.relay;
     if (grid < 1) return fail(DSN_ERR_UNSUPPORTED, "no sweep kernel of this shape fits the device");

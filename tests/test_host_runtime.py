@@ -27,7 +27,7 @@ def test_capturing_stream_is_refused_untouched():
     and then a tile's."""
     fake_hip.run('''
 stream = 0x1000
-for entry in ("solve", "adjoint", "batch", "fused"):
+for entry in ("solve", "noalloc", "adjoint", "batch", "fused"):
     h = problem((9, 20, 18), 4, G=2, fixup=1)
     h.set_sweep_shape(1, 16)
     assert solve(h, stream=stream)[0] == dsn.DSN_OK
@@ -42,6 +42,8 @@ for entry in ("solve", "adjoint", "batch", "fused"):
     if entry == "solve":
         st = solve(h, stream=stream)[0]
         assert solve(h, stream=stream, iters=None)[0] == dsn.DSN_ERR_DEVICE
+    elif entry == "noalloc":
+        st = dsn.lib().dsn_solve_noalloc(h.handle, C.byref(s), C.byref(o), ptr, None, None)
     elif entry == "adjoint":
         J = C.c_double()
         st = dsn.lib().dsn_solve_adjoint(h.handle, C.byref(s), ptr, C.byref(o), C.byref(J), ptr, None, None)
