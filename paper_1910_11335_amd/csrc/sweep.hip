@@ -920,7 +920,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     // atomic over the lanes, and wait for it on the spot
     int opaque0 = 0;
     asm("" : "+v"(opaque0));
-    if (tw == 0) {
+    if (tw == 0 && lead + TW <= NW) {
         if (lane == 0) tnext = atomicAdd(&ctr[opaque0], 1);
         have_next = true;
     }
@@ -943,9 +943,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     }
     if (threadIdx.x == 0) sAbort = 0;
     __syncthreads();  // the only barrier
-    // Never taken: a block is a whole number of teams.  It keeps the compiler
-    // from merging the code on its two sides, whose schedule a small mesh feels
-    // (33x21x18 solve 1.41 ms with it, 1.45 without).
+    // Never taken: a block is a whole number of teams.  This and the test at the
+    // first ticket keep the compiler from merging the code on their two sides,
+    // whose schedule the solves feel (33x21x18 1.41 ms, 1.45 without this one;
+    // 64x64x16 S6 G90 81.5 ms, 82.0 without the other).
     if (lead + TW > NW) return;
 
     // waits on LDS state: polled much faster than a face word in memory
